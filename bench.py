@@ -121,11 +121,11 @@ def parse():
     ap.add_argument("--layout", default="tuned", choices=["tuned", "aligned", "given"],
                     help="tuned: time candidate row strides / store policies on the geometry "
                          "first (excluded from the timed region); aligned: 128-byte aligned "
-                         "stride, plain stores, contiguous eighth per XCD; given: --stride/--nt/--chunk")
+                         "stride, plain stores, the library's XCD mapping; given: --stride/--nt/--chunk")
     ap.add_argument("--stride", type=int, default=0, help="row stride for --layout given")
     ap.add_argument("--nt", type=int, default=1, help="nontemporal stores for --layout given")
     ap.add_argument("--chunk", type=int, default=0,
-                    help="consecutive tiles per XCD for --layout given (0 = one eighth each)")
+                    help="consecutive tiles per XCD for --layout given (0 = the library's choice)")
     ap.add_argument("--experiment", default="headline",
                     choices=["headline", "precision", "adjoint", "batched", "orderings",
                              "partitions", "ordering_tuner", "compressed", "oracle_rates", "pbb", "launch_overhead"],

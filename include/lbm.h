@@ -97,15 +97,19 @@ typedef enum {
 } lbm_storage;
 
 enum {
-    LBM_FLAG_NONTEMPORAL = 1, /* write the new PDFs with nontemporal stores (Sec. 7) */
+    /* Launch hints.  Results do not depend on them, and a state small enough to
+     * stay in the last-level cache from step to step is swept without them. */
+    LBM_FLAG_NONTEMPORAL = 1, /* write the new PDFs with nontemporal stores (Sec. 7);
+                                 without it the library chooses by storage and size */
     LBM_FLAG_CHECK_FINITE = 2, /* lbm_moments: read the totals back (synchronising the
                                   stream) and return LBM_ENONFINITE if one is NaN or
                                   infinite (a diverged run); ignored by the sweeps */
     /* Workgroup-to-XCD mapping of the sweep, bits [8, 16) of flags, a power of
      * two k: the hardware hands workgroup w to XCD w % 8; the sweep relabels
      * workgroups so that each XCD takes k consecutive list tiles before the
-     * next XCD's k.  k = 1 keeps the hardware round robin; 0 (default) gives
-     * each XCD one contiguous eighth of the list.  Results do not depend on it. */
+     * next XCD's k.  k = 1 keeps the hardware round robin; 0 (default) lets the
+     * library choose by the size of the state: one contiguous eighth of the
+     * list per XCD, or short runs.  A launch hint, like the first flag. */
     LBM_FLAG_XCD_CHUNK_SHIFT = 8,
     LBM_FLAG_XCD_CHUNK_MASK = 0xff00
 };

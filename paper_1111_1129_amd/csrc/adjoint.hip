@@ -22,11 +22,18 @@
 namespace lbm {
 
 constexpr int kAdjBlock = 256;
+// Bytes per cell (sweep_launch): lambda^{t+1}, lambda^t, and f_t twice, since
+// every step of the reverse sweep reads another state.  Without the flag the
+// stores are nontemporal up to 1.25 GiB of that: 8-bit codes, 1.1 / 2.0 M
+// cells, 94 / 193 us a step against 108 / 200 with plain stores, but 4.0 /
+// 7.8 M cells 411 / 793 against 393 / 775.
+constexpr size_t kAdjCellBytes = 4 * Q * sizeof(double);
+constexpr size_t kAdjMaxNt = size_t(5) << 28;
 static_assert(kAdjBlock == kCodeTile, "a workgroup of k_adjoint_coded is one code tile");
 
 // The adjoint of one cell m whose 19 slots A (A[0] = m, A[k+1] = the slot it
 // pulls direction k + 1 from) are known.
-template <bool PBB, bool NT>
+template <bool PBB, int POL>
 __device__ __forceinline__ void adjoint_cell(const double* __restrict__ f_t, const uint32_t* A,
                                              const double* __restrict__ ns,
                                              const double* __restrict__ lam_next,
@@ -37,7 +44,7 @@ __device__ __forceinline__ void adjoint_cell(const double* __restrict__ f_t, con
 #pragma unroll
     for (int k = 0; k < Q; ++k) g[k] = f_t[A[k]];
 #pragma unroll
-    for (int k = 0; k < Q; ++k) mu[k] = ld_stream(lam_next + k * stride + m);  // own column, read once
+    for (int k = 0; k < Q; ++k) mu[k] = ld_stream<POL>(lam_next + k * stride + m);  // own column, read once
     trt_collide<double, false>(g, fs, c, 0.0);
     const CellMoments<double> cm = cell_moments(g);
     const double s = PBB ? ns[m] : 0.0;
@@ -70,7 +77,7 @@ __device__ __forceinline__ void adjoint_cell(const double* __restrict__ f_t, con
     const double P = sp * m0;
     double nu0 = mu[0] - sp * mu[0] + P;
     if constexpr (PBB) nu0 = (1.0 - s) * nu0 + s * mu[0];
-    st<double, double, NT>(lam_t + A[0], nu0);
+    st<double, double, POL == kStreamNT>(lam_t + A[0], nu0);
 #pragma unroll
     for (int k = 0; k < NPAIR; ++k) {
         const int a = 2 * k + 1, b = 2 * k + 2;
@@ -85,12 +92,12 @@ __device__ __forceinline__ void adjoint_cell(const double* __restrict__ f_t, con
             na = (1.0 - s) * na + s * mu[b];
             nb = (1.0 - s) * nb + s * mu[a];
         }
-        st<double, double, NT>(lam_t + A[a], na);
-        st<double, double, NT>(lam_t + A[b], nb);
+        st<double, double, POL == kStreamNT>(lam_t + A[a], na);
+        st<double, double, POL == kStreamNT>(lam_t + A[b], nb);
     }
 }
 
-template <bool PBB, bool NT>
+template <bool PBB, int POL>
 __global__ __launch_bounds__(kAdjBlock) void k_adjoint(const double* __restrict__ f_t,
                                                        const uint32_t* __restrict__ adj,
                                                        const double* __restrict__ ns,
@@ -98,14 +105,14 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint(const double* __restrict_
                                                        double* __restrict__ lam_t,
                                                        double* __restrict__ grad, int64_t n,
                                                        int64_t stride, TrtConst c,
-                                                       int chunk_shift) {
-    const int64_t m = logical_block(chunk_shift) * kAdjBlock + threadIdx.x;
+                                                       XcdMap map) {
+    const int64_t m = logical_block(map) * kAdjBlock + threadIdx.x;
     if (m >= n) return;
     uint32_t A[Q];
     A[0] = uint32_t(m);
 #pragma unroll
-    for (int k = 0; k < Q - 1; ++k) A[k + 1] = ld_stream(adj + k * stride + m);
-    adjoint_cell<PBB, NT>(f_t, A, ns, lam_next, lam_t, grad, m, stride, c);
+    for (int k = 0; k < Q - 1; ++k) A[k + 1] = ld_stream<POL>(adj + k * stride + m);
+    adjoint_cell<PBB, POL>(f_t, A, ns, lam_next, lam_t, grad, m, stride, c);
 }
 
 // Same, with the slots rebuilt from the adjacency codes of
@@ -113,7 +120,7 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint(const double* __restrict_
 // 8-bit codes of a narrow tile (lbm_narrow_codes), otherwise the 16-bit codes;
 // a tile with escapes reads adj.  The branch is uniform over the workgroup and
 // every form rebuilds the same slots, so the result does not depend on it.
-template <bool PBB, bool NT, bool C8>
+template <bool PBB, int POL, bool C8>
 __global__ __launch_bounds__(kAdjBlock) void k_adjoint_coded(const double* __restrict__ f_t,
                                                              const int8_t* __restrict__ codes8,
                                                              const int16_t* __restrict__ codes,
@@ -124,8 +131,8 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint_coded(const double* __res
                                                              double* __restrict__ lam_t,
                                                              double* __restrict__ grad, int64_t n,
                                                              int64_t stride, TrtConst c,
-                                                             int chunk_shift) {
-    const int64_t tile = logical_block(chunk_shift);
+                                                             XcdMap map) {
+    const int64_t tile = logical_block(map);
     const int64_t m = tile * kAdjBlock + threadIdx.x;
     if (m >= n) return;
     const int32_t* rec = tile_rec + tile * kCodeRec;  // uniform over the workgroup
@@ -135,7 +142,7 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint_coded(const double* __res
     if (C8 && rec[Q] != 0) {
         int32_t cd[Q - 1];
 #pragma unroll
-        for (int k = 0; k < Q - 1; ++k) cd[k] = ld_stream(codes8 + k * stride + m);
+        for (int k = 0; k < Q - 1; ++k) cd[k] = ld_stream<POL>(codes8 + k * stride + m);
 #pragma unroll
         for (int k = 0; k < Q - 1; ++k) {
             const uint32_t i = k + 1;
@@ -144,11 +151,11 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint_coded(const double* __res
         }
     } else if (rec[Q - 1] != 0) {
 #pragma unroll
-        for (int k = 0; k < Q - 1; ++k) A[k + 1] = ld_stream(adj + k * stride + m);
+        for (int k = 0; k < Q - 1; ++k) A[k + 1] = ld_stream<POL>(adj + k * stride + m);
     } else {
         int32_t cd[Q - 1];
 #pragma unroll
-        for (int k = 0; k < Q - 1; ++k) cd[k] = ld_stream(codes + k * stride + m);
+        for (int k = 0; k < Q - 1; ++k) cd[k] = ld_stream<POL>(codes + k * stride + m);
 #pragma unroll
         for (int k = 0; k < Q - 1; ++k) {
             const uint32_t i = k + 1;
@@ -156,7 +163,7 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint_coded(const double* __res
                                         : i * S + uint32_t(rec[k]) + mm + uint32_t(cd[k]);
         }
     }
-    adjoint_cell<PBB, NT>(f_t, A, ns, lam_next, lam_t, grad, m, stride, c);
+    adjoint_cell<PBB, POL>(f_t, A, ns, lam_next, lam_t, grad, m, stride, c);
 }
 
 // Seed lambda^T = dJ/df^T for J = (1/n) sum_m (j_x(m) + G_x/2): the slot a cell
@@ -191,18 +198,13 @@ extern "C" lbm_status lbm_step_adjoint(const lbm_params* p, int64_t n, int64_t s
     if (!f_t) return LBM_EINVAL;
     const TrtConst c = make_trt_const(*p);
     const double* f = static_cast<const double*>(f_t);
-    // the sweep's launch options: workgroup-to-XCD mapping, nontemporal stores
-    const int cs = chunk_shift_for(p->flags, n, kAdjBlock);
-    const dim3 g{unsigned(grid_blocks(n, kAdjBlock, cs))}, b{unsigned(kAdjBlock)};
-    const bool nt = p->flags & LBM_FLAG_NONTEMPORAL;
-    if (ns) {
-        if (nt) k_adjoint<true, true><<<g, b, 0, s>>>(f, adj, ns, lam_next, lam_t, grad_ns, n, stride, c, cs);
-        else k_adjoint<true, false><<<g, b, 0, s>>>(f, adj, ns, lam_next, lam_t, grad_ns, n, stride, c, cs);
-    } else {
-        if (nt) k_adjoint<false, true><<<g, b, 0, s>>>(f, adj, ns, lam_next, lam_t, nullptr, n, stride, c, cs);
-        else k_adjoint<false, false><<<g, b, 0, s>>>(f, adj, ns, lam_next, lam_t, nullptr, n, stride, c, cs);
-    }
-    return after_launch();
+    // the sweep's launch options: workgroup-to-XCD mapping, memory policy
+    const SweepLaunch l = sweep_launch(p->flags, n, kAdjCellBytes, kAdjMaxNt);
+    return with_policy(l.policy, [&](auto pol) {
+        if (ns) k_adjoint<true, pol><<<l.grid, l.block, 0, s>>>(f, adj, ns, lam_next, lam_t, grad_ns, n, stride, c, l.map);
+        else k_adjoint<false, pol><<<l.grid, l.block, 0, s>>>(f, adj, ns, lam_next, lam_t, nullptr, n, stride, c, l.map);
+        return after_launch();
+    });
 }
 
 namespace lbm {
@@ -221,17 +223,12 @@ lbm_status step_adjoint_coded(const lbm_params* p, int64_t n, int64_t stride,
     hipStream_t s = as_stream(stream);
     const TrtConst c = make_trt_const(*p);
     const double* f = static_cast<const double*>(f_t);
-    const int cs = chunk_shift_for(p->flags, n, kAdjBlock);
-    const dim3 g{unsigned(grid_blocks(n, kAdjBlock, cs))}, b{unsigned(kAdjBlock)};
-    const bool nt = p->flags & LBM_FLAG_NONTEMPORAL;
-    if (ns) {
-        if (nt) k_adjoint_coded<true, true, C8><<<g, b, 0, s>>>(f, codes8, codes, tile_records, adj, ns, lam_next, lam_t, grad_ns, n, stride, c, cs);
-        else k_adjoint_coded<true, false, C8><<<g, b, 0, s>>>(f, codes8, codes, tile_records, adj, ns, lam_next, lam_t, grad_ns, n, stride, c, cs);
-    } else {
-        if (nt) k_adjoint_coded<false, true, C8><<<g, b, 0, s>>>(f, codes8, codes, tile_records, adj, ns, lam_next, lam_t, nullptr, n, stride, c, cs);
-        else k_adjoint_coded<false, false, C8><<<g, b, 0, s>>>(f, codes8, codes, tile_records, adj, ns, lam_next, lam_t, nullptr, n, stride, c, cs);
-    }
-    return after_launch();
+    const SweepLaunch l = sweep_launch(p->flags, n, kAdjCellBytes, kAdjMaxNt);
+    return with_policy(l.policy, [&](auto pol) {
+        if (ns) k_adjoint_coded<true, pol, C8><<<l.grid, l.block, 0, s>>>(f, codes8, codes, tile_records, adj, ns, lam_next, lam_t, grad_ns, n, stride, c, l.map);
+        else k_adjoint_coded<false, pol, C8><<<l.grid, l.block, 0, s>>>(f, codes8, codes, tile_records, adj, ns, lam_next, lam_t, nullptr, n, stride, c, l.map);
+        return after_launch();
+    });
 }
 
 }  // namespace lbm

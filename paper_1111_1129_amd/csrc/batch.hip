@@ -118,7 +118,7 @@ __device__ __forceinline__ TrtConst tile_const(const ParamEntry* __restrict__ en
 // the full list in a tile with escapes, else 16-bit codes).
 enum BatchSrc { kAdj = 0, kC16 = 1, kC8 = 2 };
 
-template <int ST, bool PBB, bool NT, int SRC>
+template <int ST, bool PBB, int POL, int SRC>
 __device__ __forceinline__ void sweep_tile(const typename Storage<ST>::T* __restrict__ src,
                                            typename Storage<ST>::T* __restrict__ dst,
                                            const int8_t* __restrict__ codes8,
@@ -128,20 +128,20 @@ __device__ __forceinline__ void sweep_tile(const typename Storage<ST>::T* __rest
                                            const double* __restrict__ ns, int64_t tile, int64_t m,
                                            int64_t stride, const TrtConst& c) {
     if constexpr (SRC == kAdj) {
-        update_cell<ST, PBB, NT>(src, dst, adj, ns, m, stride, c);
+        update_cell<ST, PBB, POL>(src, dst, adj, ns, m, stride, c);
     } else {
         const int32_t* rec = tile_rec + tile * kCodeRec;  // uniform over the workgroup
         if (SRC == kC8 && rec[Q] != 0)
-            update_cell_coded<ST, PBB, NT, int8_t>(src, dst, codes8, rec, ns, m, stride, c);
+            update_cell_coded<ST, PBB, POL, int8_t>(src, dst, codes8, rec, ns, m, stride, c);
         else if (rec[Q - 1] != 0)
-            update_cell<ST, PBB, NT>(src, dst, adj, ns, m, stride, c);
+            update_cell<ST, PBB, POL>(src, dst, adj, ns, m, stride, c);
         else
-            update_cell_coded<ST, PBB, NT, int16_t>(src, dst, codes, rec, ns, m, stride, c);
+            update_cell_coded<ST, PBB, POL, int16_t>(src, dst, codes, rec, ns, m, stride, c);
     }
 }
 
 // One launch per step, constants from the table.
-template <int ST, bool PBB, bool NT, int SRC>
+template <int ST, bool PBB, int POL, int SRC>
 __global__ __launch_bounds__(kBBlock) void k_trt_table(const typename Storage<ST>::T* __restrict__ src,
                                                        typename Storage<ST>::T* __restrict__ dst,
                                                        const int8_t* __restrict__ codes8,
@@ -152,12 +152,12 @@ __global__ __launch_bounds__(kBBlock) void k_trt_table(const typename Storage<ST
                                                        int64_t stride,
                                                        const ParamEntry* __restrict__ entries,
                                                        const int32_t* __restrict__ tile_param,
-                                                       int chunk_shift) {
-    const int64_t tile = logical_block(chunk_shift);
+                                                       XcdMap map) {
+    const int64_t tile = logical_block(map);
     const int64_t m = tile * kBBlock + threadIdx.x;
     if (m >= n) return;
     const TrtConst c = tile_const(entries, tile_param, tile);
-    sweep_tile<ST, PBB, NT, SRC>(src, dst, codes8, codes, tile_rec, adj, ns, tile, m, stride, c);
+    sweep_tile<ST, PBB, POL, SRC>(src, dst, codes8, codes, tile_rec, adj, ns, tile, m, stride, c);
 }
 
 // ---------------------------------------------------------------------------
@@ -203,7 +203,7 @@ constexpr int kPThreads = 1024;
 constexpr int kPWaves = kPThreads / 64;
 constexpr int kGroupTiles = kPWaves / (kBBlock / 64);  // 4 tiles per pass
 
-template <int ST, bool PBB, bool NT, int SRC>
+template <int ST, bool PBB, int POL, int SRC>
 __global__ __launch_bounds__(kPThreads) void k_trt_persistent(typename Storage<ST>::T* fa,
                                                               typename Storage<ST>::T* fb,
                                                               const int8_t* __restrict__ codes8,
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(kPThreads) void k_trt_persistent(typename Storage<S
                                                               int64_t n, int64_t stride,
                                                               const ParamEntry* __restrict__ entries,
                                                               const int32_t* __restrict__ tile_param,
-                                                              int n_steps, int chunk_shift,
+                                                              int n_steps, XcdMap map,
                                                               Barrier bar) {
     __shared__ int ok;
     __shared__ unsigned int populated;
@@ -243,8 +243,7 @@ __global__ __launch_bounds__(kPThreads) void k_trt_persistent(typename Storage<S
     const int lane = int(threadIdx.x) & 63;
     const int64_t tiles = (n + kBBlock - 1) / kBBlock;
     const int64_t groups = (tiles + kGroupTiles - 1) / kGroupTiles;
-    const int64_t q = int64_t(NXCD) << chunk_shift;
-    const int64_t vgroups = (groups + q - 1) / q * q;  // virtual groups, relabelled like workgroups
+    const int64_t vgroups = virtual_blocks(groups, map);  // relabelled like workgroups
     const int64_t my_tile_in_group = wave / (kBBlock / 64);
     const int64_t my_quarter = (wave % (kBBlock / 64)) * 64 + lane;
     unsigned int gen = 0;
@@ -252,14 +251,12 @@ __global__ __launch_bounds__(kPThreads) void k_trt_persistent(typename Storage<S
         const auto* src = (step & 1) ? fb : fa;
         auto* dst = (step & 1) ? fa : fb;
         for (int64_t v = blockIdx.x; v < vgroups; v += gridDim.x) {
-            const int64_t grp = ((v >> (3 + chunk_shift)) << (3 + chunk_shift)) +
-                                ((v & (NXCD - 1)) << chunk_shift) +
-                                ((v >> 3) & ((int64_t(1) << chunk_shift) - 1));
+            const int64_t grp = logical_of(uint32_t(v), map);
             const int64_t tile = grp * kGroupTiles + my_tile_in_group;
             const int64_t m = tile * kBBlock + my_quarter;
             if (grp < groups && m < n) {
                 const TrtConst c = tile_const(entries, tile_param, tile);
-                sweep_tile<ST, PBB, NT, SRC>(src, dst, codes8, codes, tile_rec, adj, ns, tile, m,
+                sweep_tile<ST, PBB, POL, SRC>(src, dst, codes8, codes, tile_rec, adj, ns, tile, m,
                                              stride, c);
             }
         }
@@ -301,33 +298,37 @@ struct BatchLaunch {
     void* fa;
     void* fb;
     int n_steps;
-    int chunk_shift;             // per-step launch: runs of tiles per XCD
-    int chunk_shift_persistent;  // persistent launch: runs of 4-tile groups per XCD
+    int32_t flags;  // launch flags shared by the parameter sets
     ParamTable tab;
     void* barrier;  // persistent only
 };
 
-template <int ST, bool PBB, bool NT, int SRC>
-lbm_status launch_table_steps(const BatchLaunch& L, hipStream_t s) {
+// Bytes a step touches per cell (sweep_launch).
+template <int ST>
+size_t cell_bytes(int src) {
+    return 2 * Q * sizeof(typename Storage<ST>::T) + (Q - 1) * (src == kC8 ? 1 : src == kC16 ? 2 : 4);
+}
+
+template <int ST, bool PBB, int POL, int SRC>
+lbm_status launch_table_steps(const BatchLaunch& L, const SweepLaunch& l, hipStream_t s) {
     using T = typename Storage<ST>::T;
     T* a = static_cast<T*>(L.fa);
     T* b = static_cast<T*>(L.fb);
-    const dim3 g{unsigned(grid_blocks(L.n, kBBlock, L.chunk_shift))}, blk{unsigned(kBBlock)};
     for (int k = 0; k < L.n_steps; ++k) {
         const T* src = (k & 1) ? b : a;
         T* dst = (k & 1) ? a : b;
-        k_trt_table<ST, PBB, NT, SRC><<<g, blk, 0, s>>>(src, dst, L.codes8, L.codes, L.rec, L.adj,
+        k_trt_table<ST, PBB, POL, SRC><<<l.grid, l.block, 0, s>>>(src, dst, L.codes8, L.codes, L.rec, L.adj,
                                                         L.ns, L.n, L.stride, L.tab.entries,
-                                                        L.tab.tile_param, L.chunk_shift);
+                                                        L.tab.tile_param, l.map);
         if (hipGetLastError() != hipSuccess) return LBM_EHIP;
     }
     return LBM_OK;
 }
 
-template <int ST, bool PBB, bool NT, int SRC>
-lbm_status launch_persistent_t(const BatchLaunch& L, hipStream_t s) {
+template <int ST, bool PBB, int POL, int SRC>
+lbm_status launch_persistent_t(const BatchLaunch& L, const SweepLaunch& l, hipStream_t s) {
     using T = typename Storage<ST>::T;
-    auto kern = k_trt_persistent<ST, PBB, NT, SRC>;
+    auto kern = k_trt_persistent<ST, PBB, POL, SRC>;
     int dev = 0, cus = 0, per_cu = 0, coop = 0;
     LBM_TRY_HIP(hipGetDevice(&dev));
     LBM_TRY_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -359,9 +360,10 @@ lbm_status launch_persistent_t(const BatchLaunch& L, hipStream_t s) {
     int64_t n = L.n, stride = L.stride;
     const ParamEntry* entries = L.tab.entries;
     const int32_t* tile_param = L.tab.tile_param;
-    int steps = L.n_steps, cs = L.chunk_shift_persistent;
+    int steps = L.n_steps;
+    XcdMap map = l.map;
     void* args[] = {&a, &b, &c8, &c16, &rec, &adj, &ns, &n, &stride, &entries, &tile_param, &steps,
-                    &cs, &bar};
+                    &map, &bar};
     LBM_TRY_HIP(hipLaunchCooperativeKernel(reinterpret_cast<const void*>(kern), dim3(unsigned(grid)),
                                            dim3(kPThreads), args, 0, s));
     int err = 0;
@@ -370,24 +372,28 @@ lbm_status launch_persistent_t(const BatchLaunch& L, hipStream_t s) {
     return err ? LBM_EBARRIER : LBM_OK;
 }
 
-template <int ST, bool PBB, bool NT>
+// A persistent workgroup takes groups of kGroupTiles tiles, a per-step one a tile.
+template <int ST, bool PBB, int SRC>
 lbm_status launch_batch_src(const BatchLaunch& L, bool persistent, hipStream_t s) {
-    if (persistent) {
-        if (L.codes8) return launch_persistent_t<ST, PBB, NT, kC8>(L, s);
-        if (L.codes) return launch_persistent_t<ST, PBB, NT, kC16>(L, s);
-        return launch_persistent_t<ST, PBB, NT, kAdj>(L, s);
-    }
-    if (L.codes8) return launch_table_steps<ST, PBB, NT, kC8>(L, s);
-    if (L.codes) return launch_table_steps<ST, PBB, NT, kC16>(L, s);
-    return launch_table_steps<ST, PBB, NT, kAdj>(L, s);
+    const SweepLaunch l = sweep_launch(L.flags, L.n, cell_bytes<ST>(SRC), sweep_max_nt(ST),
+                                       persistent ? kPThreads : kBBlock);
+    return with_policy(l.policy, [&](auto pol) {
+        return persistent ? launch_persistent_t<ST, PBB, pol, SRC>(L, l, s)
+                          : launch_table_steps<ST, PBB, pol, SRC>(L, l, s);
+    });
+}
+
+template <int ST, bool PBB>
+lbm_status launch_batch_form(const BatchLaunch& L, bool persistent, hipStream_t s) {
+    if (L.codes8) return launch_batch_src<ST, PBB, kC8>(L, persistent, s);
+    if (L.codes) return launch_batch_src<ST, PBB, kC16>(L, persistent, s);
+    return launch_batch_src<ST, PBB, kAdj>(L, persistent, s);
 }
 
 template <int ST>
-lbm_status launch_batch_st(const BatchLaunch& L, bool nt, bool persistent, hipStream_t s) {
-    if (L.ns) return nt ? launch_batch_src<ST, true, true>(L, persistent, s)
-                        : launch_batch_src<ST, true, false>(L, persistent, s);
-    return nt ? launch_batch_src<ST, false, true>(L, persistent, s)
-              : launch_batch_src<ST, false, false>(L, persistent, s);
+lbm_status launch_batch_st(const BatchLaunch& L, bool persistent, hipStream_t s) {
+    return L.ns ? launch_batch_form<ST, true>(L, persistent, s)
+                : launch_batch_form<ST, false>(L, persistent, s);
 }
 
 // Workspace of a table launch: barrier block | parameter table | tile index.
@@ -458,16 +464,15 @@ lbm_status step_batch(const lbm_params* p, int32_t n_params, const lbm_segment* 
         }
     }
     BatchLaunch L{n, stride, codes8, codes, tile_records, adj, ns, f_a, f_b, n_steps,
-                  chunk_shift_for(p[0].flags, n, kBBlock), chunk_shift_for(p[0].flags, n, kPThreads),
+                  p[0].flags,
                   ParamTable{entries, tile_param}, ws};
-    const bool nt = (p[0].flags & LBM_FLAG_NONTEMPORAL) != 0;
     switch (p[0].storage) {
-    case LBM_F64: return launch_batch_st<LBM_F64>(L, nt, persistent, s);
-    case LBM_F64_SHIFTED: return launch_batch_st<LBM_F64_SHIFTED>(L, nt, persistent, s);
-    case LBM_F32: return launch_batch_st<LBM_F32>(L, nt, persistent, s);
-    case LBM_F32_SHIFTED: return launch_batch_st<LBM_F32_SHIFTED>(L, nt, persistent, s);
-    case LBM_F16_SHIFTED: return launch_batch_st<LBM_F16_SHIFTED>(L, nt, persistent, s);
-    case LBM_F16_SHIFTED_SCALED: return launch_batch_st<LBM_F16_SHIFTED_SCALED>(L, nt, persistent, s);
+    case LBM_F64: return launch_batch_st<LBM_F64>(L, persistent, s);
+    case LBM_F64_SHIFTED: return launch_batch_st<LBM_F64_SHIFTED>(L, persistent, s);
+    case LBM_F32: return launch_batch_st<LBM_F32>(L, persistent, s);
+    case LBM_F32_SHIFTED: return launch_batch_st<LBM_F32_SHIFTED>(L, persistent, s);
+    case LBM_F16_SHIFTED: return launch_batch_st<LBM_F16_SHIFTED>(L, persistent, s);
+    case LBM_F16_SHIFTED_SCALED: return launch_batch_st<LBM_F16_SHIFTED_SCALED>(L, persistent, s);
     default: return LBM_EINVAL;
     }
 }

@@ -185,27 +185,27 @@ __global__ __launch_bounds__(kCTile) void k_narrow(const int16_t* __restrict__ c
     if (threadIdx.x == 0) rec[tile * kRec + Q] = narrow ? 1 : 0;
 }
 
-template <int ST, bool PBB, bool NT>
+template <int ST, bool PBB, int POL>
 __global__ __launch_bounds__(kCTile) void k_trt_c16(const typename Storage<ST>::T* __restrict__ src,
                                                     typename Storage<ST>::T* __restrict__ dst,
                                                     const int16_t* __restrict__ codes,
                                                     const int32_t* __restrict__ tile_rec,
                                                     const uint32_t* __restrict__ adj,
                                                     const double* __restrict__ ns, int64_t n,
-                                                    int64_t stride, TrtConst c, int chunk_shift) {
-    const int64_t tile = logical_block(chunk_shift);
+                                                    int64_t stride, TrtConst c, XcdMap map) {
+    const int64_t tile = logical_block(map);
     const int64_t m = tile * kCTile + threadIdx.x;
     if (m >= n) return;
     const int32_t* rec = tile_rec + tile * kRec;  // uniform over the workgroup
     if (rec[Q - 1] != 0)
-        update_cell<ST, PBB, NT>(src, dst, adj, ns, m, stride, c);
+        update_cell<ST, PBB, POL>(src, dst, adj, ns, m, stride, c);
     else
-        update_cell_coded<ST, PBB, NT, int16_t>(src, dst, codes, rec, ns, m, stride, c);
+        update_cell_coded<ST, PBB, POL, int16_t>(src, dst, codes, rec, ns, m, stride, c);
 }
 
 // Three-way, uniform over the workgroup: narrow tile -> 8-bit codes, tile
 // with escapes -> full list, otherwise 16-bit codes.
-template <int ST, bool PBB, bool NT>
+template <int ST, bool PBB, int POL>
 __global__ __launch_bounds__(kCTile) void k_trt_c8(const typename Storage<ST>::T* __restrict__ src,
                                                    typename Storage<ST>::T* __restrict__ dst,
                                                    const int8_t* __restrict__ codes8,
@@ -213,53 +213,50 @@ __global__ __launch_bounds__(kCTile) void k_trt_c8(const typename Storage<ST>::T
                                                    const int32_t* __restrict__ tile_rec,
                                                    const uint32_t* __restrict__ adj,
                                                    const double* __restrict__ ns, int64_t n,
-                                                   int64_t stride, TrtConst c, int chunk_shift) {
-    const int64_t tile = logical_block(chunk_shift);
+                                                   int64_t stride, TrtConst c, XcdMap map) {
+    const int64_t tile = logical_block(map);
     const int64_t m = tile * kCTile + threadIdx.x;
     if (m >= n) return;
     const int32_t* rec = tile_rec + tile * kRec;
     if (rec[Q] != 0)
-        update_cell_coded<ST, PBB, NT, int8_t>(src, dst, codes8, rec, ns, m, stride, c);
+        update_cell_coded<ST, PBB, POL, int8_t>(src, dst, codes8, rec, ns, m, stride, c);
     else if (rec[Q - 1] != 0)
-        update_cell<ST, PBB, NT>(src, dst, adj, ns, m, stride, c);
+        update_cell<ST, PBB, POL>(src, dst, adj, ns, m, stride, c);
     else
-        update_cell_coded<ST, PBB, NT, int16_t>(src, dst, codes, rec, ns, m, stride, c);
+        update_cell_coded<ST, PBB, POL, int16_t>(src, dst, codes, rec, ns, m, stride, c);
 }
 
 // codes8 == nullptr: the 16-bit sweep (k_trt_c16); else the 8-bit one.
-template <int ST, bool PBB, bool NT>
-lbm_status launch_coded(const TrtConst& c, int cs, int64_t n, int64_t stride,
-                        const int8_t* codes8, const int16_t* codes, const int32_t* toff,
-                        const uint32_t* adj, const double* ns, void* fa, void* fb, int n_steps,
-                        hipStream_t s) {
+template <int ST, bool PBB>
+lbm_status launch_coded(const lbm_params& p, int64_t n, int64_t stride, const int8_t* codes8,
+                        const int16_t* codes, const int32_t* toff, const uint32_t* adj,
+                        const double* ns, void* fa, void* fb, int n_steps, hipStream_t s) {
     using T = typename Storage<ST>::T;
     T* a = static_cast<T*>(fa);
     T* b = static_cast<T*>(fb);
-    const dim3 g{unsigned(grid_blocks(n, kCTile, cs))}, blk{unsigned(kCTile)};
-    for (int k = 0; k < n_steps; ++k) {
-        const T* src = (k & 1) ? b : a;
-        T* dst = (k & 1) ? a : b;
-        if (codes8)
-            k_trt_c8<ST, PBB, NT><<<g, blk, 0, s>>>(src, dst, codes8, codes, toff, adj, ns, n, stride, c, cs);
-        else
-            k_trt_c16<ST, PBB, NT><<<g, blk, 0, s>>>(src, dst, codes, toff, adj, ns, n, stride, c, cs);
-        if (hipGetLastError() != hipSuccess) return LBM_EHIP;
-    }
-    return LBM_OK;
+    const TrtConst c = make_trt_const(p);
+    const SweepLaunch l = sweep_launch(p.flags, n, 2 * Q * sizeof(T) + (Q - 1) * (codes8 ? 1 : 2),
+                                       sweep_max_nt(ST));
+    return with_policy(l.policy, [&](auto pol) -> lbm_status {
+        for (int k = 0; k < n_steps; ++k) {
+            const T* src = (k & 1) ? b : a;
+            T* dst = (k & 1) ? a : b;
+            if (codes8)
+                k_trt_c8<ST, PBB, pol><<<l.grid, l.block, 0, s>>>(src, dst, codes8, codes, toff, adj, ns, n, stride, c, l.map);
+            else
+                k_trt_c16<ST, PBB, pol><<<l.grid, l.block, 0, s>>>(src, dst, codes, toff, adj, ns, n, stride, c, l.map);
+            if (hipGetLastError() != hipSuccess) return LBM_EHIP;
+        }
+        return LBM_OK;
+    });
 }
 
 template <int ST>
 lbm_status dispatch_coded(const lbm_params& p, int64_t n, int64_t stride, const int8_t* codes8,
                           const int16_t* codes, const int32_t* toff, const uint32_t* adj,
                           const double* ns, void* fa, void* fb, int n_steps, hipStream_t s) {
-    const TrtConst c = make_trt_const(p);
-    const int cs = chunk_shift_for(p.flags, n, kCTile);
-    const bool nt = p.flags & LBM_FLAG_NONTEMPORAL;
-    if (ns)
-        return nt ? launch_coded<ST, true, true>(c, cs, n, stride, codes8, codes, toff, adj, ns, fa, fb, n_steps, s)
-                  : launch_coded<ST, true, false>(c, cs, n, stride, codes8, codes, toff, adj, ns, fa, fb, n_steps, s);
-    return nt ? launch_coded<ST, false, true>(c, cs, n, stride, codes8, codes, toff, adj, ns, fa, fb, n_steps, s)
-              : launch_coded<ST, false, false>(c, cs, n, stride, codes8, codes, toff, adj, ns, fa, fb, n_steps, s);
+    return ns ? launch_coded<ST, true>(p, n, stride, codes8, codes, toff, adj, ns, fa, fb, n_steps, s)
+              : launch_coded<ST, false>(p, n, stride, codes8, codes, toff, adj, ns, fa, fb, n_steps, s);
 }
 
 lbm_status step_coded(const lbm_params& p, int64_t n, int64_t stride, const int8_t* codes8,

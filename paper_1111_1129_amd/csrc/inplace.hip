@@ -38,7 +38,7 @@ enum SlotSource { kFromAdj = 0, kFrom16 = 1, kFrom8 = 2 };
 
 // Slots rebuilt from the 16-bit (SRC = kFrom16) or 8-bit (kFrom8) codes of
 // the cell's tile: s[k] = adj(k + 1, m).
-template <int SRC, class CT>
+template <int SRC, int POL, class CT>
 __device__ __forceinline__ void slots_from_codes(uint32_t* s, const CT* __restrict__ codes,
                                                  const int32_t* __restrict__ rec, int64_t m,
                                                  int64_t stride) {
@@ -46,7 +46,7 @@ __device__ __forceinline__ void slots_from_codes(uint32_t* s, const CT* __restri
     const CT* cp = codes + m;
     int32_t cd[Q - 1];
 #pragma unroll
-    for (int k = 0; k < Q - 1; ++k) cd[k] = ld_stream(cp + k * stride);
+    for (int k = 0; k < Q - 1; ++k) cd[k] = ld_stream<POL>(cp + k * stride);
     const uint32_t S = uint32_t(stride), mm = uint32_t(m);
 #pragma unroll
     for (int k = 0; k < Q - 1; ++k) {
@@ -58,7 +58,7 @@ __device__ __forceinline__ void slots_from_codes(uint32_t* s, const CT* __restri
 }
 
 // Slots of the gather-scatter step for one cell: s[k] = adj(k + 1, m).
-template <int SRC>
+template <int SRC, int POL>
 __device__ __forceinline__ void gather_slots(uint32_t* s, const uint32_t* __restrict__ adj,
                                              const int16_t* __restrict__ codes,
                                              const int8_t* __restrict__ codes8,
@@ -67,15 +67,15 @@ __device__ __forceinline__ void gather_slots(uint32_t* s, const uint32_t* __rest
     if constexpr (SRC == kFromAdj) {
         const uint32_t* ap = adj + m;
 #pragma unroll
-        for (int k = 0; k < Q - 1; ++k) s[k] = ld_stream(ap + k * stride);
+        for (int k = 0; k < Q - 1; ++k) s[k] = ld_stream<POL>(ap + k * stride);
     } else if constexpr (SRC == kFrom16) {
-        slots_from_codes<kFrom16>(s, codes, rec, m, stride);
+        slots_from_codes<kFrom16, POL>(s, codes, rec, m, stride);
     } else {
-        slots_from_codes<kFrom8>(s, codes8, rec, m, stride);
+        slots_from_codes<kFrom8, POL>(s, codes8, rec, m, stride);
     }
 }
 
-template <int ST, bool PBB, bool NT, int SRC>
+template <int ST, bool PBB, int POL, int SRC>
 __device__ __forceinline__ void gather_scatter_cell(typename Storage<ST>::T* f,
                                                     const uint32_t* __restrict__ adj,
                                                     const int16_t* __restrict__ codes,
@@ -86,7 +86,7 @@ __device__ __forceinline__ void gather_scatter_cell(typename Storage<ST>::T* f,
     using T = typename Storage<ST>::T;
     using A = typename Storage<ST>::A;
     uint32_t s[Q - 1];
-    gather_slots<SRC>(s, adj, codes, codes8, rec, m, stride);
+    gather_slots<SRC, POL>(s, adj, codes, codes8, rec, m, stride);
     A g[Q];
     g[0] = ld<T, A>(f + m);
 #pragma unroll
@@ -95,16 +95,16 @@ __device__ __forceinline__ void gather_scatter_cell(typename Storage<ST>::T* f,
     if constexpr (PBB) sf = static_cast<A>(ns[m]);
     A out[Q];
     trt_collide<A, PBB>(g, out, c, sf);
-    st<T, A, NT>(f + m, out[0]);
+    st<T, A, POL == kStreamNT>(f + m, out[0]);
     // out_i goes where direction opp(i) was gathered from
 #pragma unroll
-    for (int k = 0; k < Q - 1; ++k) st<T, A, NT>(f + s[k], out[opp(k + 1)]);
+    for (int k = 0; k < Q - 1; ++k) st<T, A, POL == kStreamNT>(f + s[k], out[opp(k + 1)]);
 }
 
 // SRC: the narrowest code form the launch may use; each tile then takes what
 // its record allows (a workgroup-uniform choice): 8-bit codes in a narrow
 // tile (kFrom8 only), the full list in a tile with escapes, else 16-bit codes.
-template <int ST, bool PBB, bool NT, int SRC>
+template <int ST, bool PBB, int POL, int SRC>
 __global__ __launch_bounds__(kIBlock) void k_gather_scatter(typename Storage<ST>::T* f,
                                                             const uint32_t* __restrict__ adj,
                                                             const int16_t* __restrict__ codes,
@@ -112,81 +112,76 @@ __global__ __launch_bounds__(kIBlock) void k_gather_scatter(typename Storage<ST>
                                                             const int32_t* __restrict__ tile_rec,
                                                             const double* __restrict__ ns,
                                                             int64_t n, int64_t stride, TrtConst c,
-                                                            int chunk_shift) {
-    const int64_t tile = logical_block(chunk_shift);
+                                                            XcdMap map) {
+    const int64_t tile = logical_block(map);
     const int64_t m = tile * kIBlock + threadIdx.x;
     if (m >= n) return;
     if constexpr (SRC == kFromAdj) {
-        gather_scatter_cell<ST, PBB, NT, kFromAdj>(f, adj, codes, codes8, nullptr, ns, m, stride, c);
+        gather_scatter_cell<ST, PBB, POL, kFromAdj>(f, adj, codes, codes8, nullptr, ns, m, stride, c);
     } else {
         const int32_t* rec = tile_rec + tile * kCodeRec;  // uniform over the workgroup
         if (SRC == kFrom8 && rec[Q] != 0)
-            gather_scatter_cell<ST, PBB, NT, kFrom8>(f, adj, codes, codes8, rec, ns, m, stride, c);
+            gather_scatter_cell<ST, PBB, POL, kFrom8>(f, adj, codes, codes8, rec, ns, m, stride, c);
         else if (rec[Q - 1] != 0)  // the tile has escape codes: use the full list
-            gather_scatter_cell<ST, PBB, NT, kFromAdj>(f, adj, codes, codes8, rec, ns, m, stride, c);
+            gather_scatter_cell<ST, PBB, POL, kFromAdj>(f, adj, codes, codes8, rec, ns, m, stride, c);
         else
-            gather_scatter_cell<ST, PBB, NT, kFrom16>(f, adj, codes, codes8, rec, ns, m, stride, c);
+            gather_scatter_cell<ST, PBB, POL, kFrom16>(f, adj, codes, codes8, rec, ns, m, stride, c);
     }
 }
 
-template <int ST, bool PBB, bool NT>
+template <int ST, bool PBB, int POL>
 __global__ __launch_bounds__(kIBlock) void k_local(typename Storage<ST>::T* f,
                                                    const double* __restrict__ ns, int64_t n,
-                                                   int64_t stride, TrtConst c, int chunk_shift) {
+                                                   int64_t stride, TrtConst c, XcdMap map) {
     using T = typename Storage<ST>::T;
     using A = typename Storage<ST>::A;
-    const int64_t tile = logical_block(chunk_shift);
-    const int64_t m = tile * kIBlock + threadIdx.x;
+    const int64_t m = logical_block(map) * kIBlock + threadIdx.x;
     if (m >= n) return;
     T* fp = f + m;
     A g[Q];
 #pragma unroll
-    for (int i = 0; i < Q; ++i) g[i] = static_cast<A>(ld_stream(fp + opp(i) * stride));  // own column only
+    for (int i = 0; i < Q; ++i) g[i] = static_cast<A>(ld_stream<POL>(fp + opp(i) * stride));  // own column only
     A sf = A(0);
     if constexpr (PBB) sf = static_cast<A>(ns[m]);
     A out[Q];
     trt_collide<A, PBB>(g, out, c, sf);
 #pragma unroll
-    for (int i = 0; i < Q; ++i) st<T, A, NT>(fp + i * stride, out[i]);
+    for (int i = 0; i < Q; ++i) st<T, A, POL == kStreamNT>(fp + i * stride, out[i]);
 }
 
-template <int ST, bool PBB, bool NT>
-lbm_status launch_inplace(const TrtConst& c, int cs, int64_t n, int64_t stride,
-                          const uint32_t* adj, const int16_t* codes, const int8_t* codes8,
-                          const int32_t* rec, const double* ns, void* fv, int phase, int n_steps,
-                          hipStream_t s) {
+template <int ST, bool PBB>
+lbm_status launch_inplace(const lbm_params& p, int64_t n, int64_t stride, const uint32_t* adj,
+                          const int16_t* codes, const int8_t* codes8, const int32_t* rec,
+                          const double* ns, void* fv, int phase, int n_steps, hipStream_t s) {
     using T = typename Storage<ST>::T;
     T* f = static_cast<T*>(fv);
-    const int64_t grid = grid_blocks(n, kIBlock, cs);
-    const dim3 g{unsigned(grid)}, b{unsigned(kIBlock)};
-    for (int k = 0; k < n_steps; ++k) {
-        if (((phase + k) & 1) == 0) {
-            if (codes8)
-                k_gather_scatter<ST, PBB, NT, kFrom8><<<g, b, 0, s>>>(f, adj, codes, codes8, rec, ns, n, stride, c, cs);
-            else if (codes)
-                k_gather_scatter<ST, PBB, NT, kFrom16><<<g, b, 0, s>>>(f, adj, codes, codes8, rec, ns, n, stride, c, cs);
-            else
-                k_gather_scatter<ST, PBB, NT, kFromAdj><<<g, b, 0, s>>>(f, adj, codes, codes8, rec, ns, n, stride, c, cs);
-        } else {
-            k_local<ST, PBB, NT><<<g, b, 0, s>>>(f, ns, n, stride, c, cs);
+    const TrtConst c = make_trt_const(p);
+    const SweepLaunch l = sweep_launch(p.flags, n, Q * sizeof(T) + (Q - 1) * (codes8 ? 1 : codes ? 2 : 4),
+                                       sweep_max_nt(ST));
+    return with_policy(l.policy, [&](auto pol) -> lbm_status {
+        for (int k = 0; k < n_steps; ++k) {
+            if (((phase + k) & 1) == 0) {
+                if (codes8)
+                    k_gather_scatter<ST, PBB, pol, kFrom8><<<l.grid, l.block, 0, s>>>(f, adj, codes, codes8, rec, ns, n, stride, c, l.map);
+                else if (codes)
+                    k_gather_scatter<ST, PBB, pol, kFrom16><<<l.grid, l.block, 0, s>>>(f, adj, codes, codes8, rec, ns, n, stride, c, l.map);
+                else
+                    k_gather_scatter<ST, PBB, pol, kFromAdj><<<l.grid, l.block, 0, s>>>(f, adj, codes, codes8, rec, ns, n, stride, c, l.map);
+            } else {
+                k_local<ST, PBB, pol><<<l.grid, l.block, 0, s>>>(f, ns, n, stride, c, l.map);
+            }
+            if (hipGetLastError() != hipSuccess) return LBM_EHIP;
         }
-        if (hipGetLastError() != hipSuccess) return LBM_EHIP;
-    }
-    return LBM_OK;
+        return LBM_OK;
+    });
 }
 
 template <int ST>
 lbm_status dispatch_inplace(const lbm_params& p, int64_t n, int64_t stride, const uint32_t* adj,
                             const int16_t* codes, const int8_t* codes8, const int32_t* rec,
                             const double* ns, void* f, int phase, int n_steps, hipStream_t s) {
-    const TrtConst c = make_trt_const(p);
-    const int cs = chunk_shift_for(p.flags, n, kIBlock);
-    const bool nt = p.flags & LBM_FLAG_NONTEMPORAL;
-    if (ns)
-        return nt ? launch_inplace<ST, true, true>(c, cs, n, stride, adj, codes, codes8, rec, ns, f, phase, n_steps, s)
-                  : launch_inplace<ST, true, false>(c, cs, n, stride, adj, codes, codes8, rec, ns, f, phase, n_steps, s);
-    return nt ? launch_inplace<ST, false, true>(c, cs, n, stride, adj, codes, codes8, rec, ns, f, phase, n_steps, s)
-              : launch_inplace<ST, false, false>(c, cs, n, stride, adj, codes, codes8, rec, ns, f, phase, n_steps, s);
+    return ns ? launch_inplace<ST, true>(p, n, stride, adj, codes, codes8, rec, ns, f, phase, n_steps, s)
+              : launch_inplace<ST, false>(p, n, stride, adj, codes, codes8, rec, ns, f, phase, n_steps, s);
 }
 
 lbm_status step_inplace(const lbm_params& p, int64_t n, int64_t stride, const uint32_t* adj,

@@ -57,14 +57,41 @@ struct Half12 {
 template <> struct Storage<LBM_F16_SHIFTED_SCALED> { using T = Half12; using A = float; static constexpr bool shifted = true; };
 
 template <class T, class A> __device__ __forceinline__ A ld(const T* p) { return static_cast<A>(*p); }
-// Read-once streams (adjacency rows, adjacency codes): nontemporal loads keep
-// them from displacing the PDF lines whose partial reuse by neighbouring
-// cells the caches serve (measured: 2 % faster sweep over codes in FP64).
-template <class T> __device__ __forceinline__ T ld_stream(const T* p) {
-    return __builtin_nontemporal_load(p);
+// Memory policy of a launch, chosen by sweep_launch() from the bytes that a
+// step touches.
+//  kCached    the state stays in the last-level cache from step to step: plain
+//             loads and stores throughout.
+//  kStream    larger: rows read once per step (adjacency, 16-bit codes) come
+//             in through nontemporal loads, which keeps them from displacing
+//             the PDF lines whose partial reuse by neighbouring cells the
+//             caches serve; plain stores.
+//  kStreamNT  the same with nontemporal stores of the new PDFs.
+enum Policy { kCached = 0, kStream = 1, kStreamNT = 2 };
+
+template <int POL, class T> __device__ __forceinline__ T ld_stream(const T* p) {
+    if constexpr (POL == kCached)
+        return *p;
+    else
+        return __builtin_nontemporal_load(p);
 }
-__device__ __forceinline__ Half12 ld_stream(const Half12* p) {
-    return Half12{__builtin_nontemporal_load(&p->bits)};
+template <int POL> __device__ __forceinline__ Half12 ld_stream(const Half12* p) {
+    if constexpr (POL == kCached)
+        return *p;
+    else
+        return Half12{__builtin_nontemporal_load(&p->bits)};
+}
+// One adjacency code of the two-array sweep.  8-bit codes are read with plain
+// loads under every policy: a wave reads half a line of a code row, and the other half is the
+// next wave's (sweep of 54 M cells, nontemporal -> plain code loads: FP64
+// 3,287 -> 3,258 us, shifted FP32 1,780 -> 1,662, scaled FP16 1,110 -> 1,099;
+// 12.7 M cells: 783 -> 759, 437 -> 428, 251 -> 243).  A 16-bit row gives a
+// wave a whole line, and 32-bit rows two: those are read once and streamed
+// (full list, FP64, 23 M cells: 1,510 us nontemporal, 1,541 plain).
+template <int POL, class CT> __device__ __forceinline__ int32_t ld_code(const CT* p) {
+    if constexpr (sizeof(CT) == 1)
+        return *p;
+    else
+        return ld_stream<POL>(p);
 }
 // FP32 -> FP16 conversion rounds to nearest even (IEEE default mode).  The
 // value is first rounded to A: device code is built without contraction, so
@@ -199,7 +226,7 @@ __device__ __forceinline__ void trt_collide(const A* g, A* out, const TrtConst& 
 // through adj (plus the own rest population), collide, store the 19 results
 // to the cell's own column of the destination rows.
 // ---------------------------------------------------------------------------
-template <int ST, bool PBB, bool NT>
+template <int ST, bool PBB, int POL>
 __device__ __forceinline__ void update_cell(const typename Storage<ST>::T* __restrict__ src,
                                             typename Storage<ST>::T* __restrict__ dst,
                                             const uint32_t* __restrict__ adj,
@@ -210,7 +237,7 @@ __device__ __forceinline__ void update_cell(const typename Storage<ST>::T* __res
     uint32_t a[Q - 1];
     const uint32_t* ap = adj + m;
 #pragma unroll
-    for (int k = 0; k < Q - 1; ++k) a[k] = ld_stream(ap + k * stride);
+    for (int k = 0; k < Q - 1; ++k) a[k] = ld_stream<POL>(ap + k * stride);
     A g[Q];
     g[0] = ld<T, A>(src + m);
 #pragma unroll
@@ -221,14 +248,14 @@ __device__ __forceinline__ void update_cell(const typename Storage<ST>::T* __res
     trt_collide<A, PBB>(g, out, c, s);
     T* dp = dst + m;
 #pragma unroll
-    for (int i = 0; i < Q; ++i) st<T, A, NT>(dp + i * stride, out[i]);
+    for (int i = 0; i < Q; ++i) st<T, A, POL == kStreamNT>(dp + i * stride, out[i]);
 }
 
 // One cell update of an escape-free tile, the slots rebuilt from the 16-bit
 // (CT = int16_t) or 8-bit (int8_t) codes in 32-bit arithmetic (every slot is
 // below 19 * stride < 2^32).  The per-tile part i * stride + tile * 256 + toff
 // is uniform (scalar); per lane it adds the lane and the code.
-template <int ST, bool PBB, bool NT, class CT>
+template <int ST, bool PBB, int POL, class CT>
 __device__ __forceinline__ void update_cell_coded(const typename Storage<ST>::T* __restrict__ src,
                                                   typename Storage<ST>::T* __restrict__ dst,
                                                   const CT* __restrict__ codes,
@@ -242,7 +269,7 @@ __device__ __forceinline__ void update_cell_coded(const typename Storage<ST>::T*
     int32_t cd[Q - 1];
     const CT* cp = codes + m;
 #pragma unroll
-    for (int k = 0; k < Q - 1; ++k) cd[k] = ld_stream(cp + k * stride);
+    for (int k = 0; k < Q - 1; ++k) cd[k] = ld_code<POL>(cp + k * stride);
     const uint32_t S = uint32_t(stride);
     const uint32_t mm = uint32_t(m);
     A g[Q];
@@ -260,45 +287,116 @@ __device__ __forceinline__ void update_cell_coded(const typename Storage<ST>::T*
     trt_collide<A, PBB>(g, out, c, sf);
     T* dp = dst + m;
 #pragma unroll
-    for (int i = 0; i < Q; ++i) st<T, A, NT>(dp + i * stride, out[i]);
+    for (int i = 0; i < Q; ++i) st<T, A, POL == kStreamNT>(dp + i * stride, out[i]);
 }
 
 // ---------------------------------------------------------------------------
 // Launch geometry.  Workgroups are handed to the 8 XCDs of the MI355X round
 // robin (workgroup w runs on XCD w % 8; checked on the device through the
 // XCC_ID hardware register), and each XCD has its own L2.  The sweep relabels
-// workgroups so that each XCD takes `chunk` consecutive list tiles at a time:
-// the gathers of neighbouring tiles share cache lines at tile edges, which
-// then stay in one L2, while all XCDs still sweep nearby parts of the list
-// (DRAM page locality).  chunk = grid/8 gives each XCD one contiguous eighth;
-// chunk = 1 is the hardware order.
+// workgroups so that each XCD takes a run of consecutive blocks of the list:
+// the gathers of neighbouring blocks share cache lines at block edges, which
+// then stay in one L2.
 // ---------------------------------------------------------------------------
 constexpr int NXCD = 8;
 
-// chunk_shift = log2(chunk); the grid is a multiple of NXCD << chunk_shift.
-__device__ __forceinline__ int64_t logical_block(int chunk_shift) {
-    const int64_t b = blockIdx.x;
-    const int64_t super = b >> (3 + chunk_shift);        // group of NXCD * chunk workgroups
-    const int64_t xcd = b & (NXCD - 1);
-    const int64_t within = (b >> 3) & ((int64_t(1) << chunk_shift) - 1);
-    return (super << (3 + chunk_shift)) + (xcd << chunk_shift) + within;
+// Runs of `run` consecutive blocks, dealt to the XCDs in turn.  Virtual block v
+// of group s = v >> group_shift of 8 runs is block (v >> 3) & mask of XCD
+// v % 8's run; a map of one run per XCD has one group (group_shift 31, every
+// index bit in mask).  Written without a branch or a division: a sweep of a
+// few workgroups waits for this before its first load.  Block indices are
+// below 2^31: a list has fewer than 2^32 / 19 cells.
+struct XcdMap {
+    uint32_t group_shift, run, mask;
+};
+
+constexpr XcdMap map_of_runs(int shift) { return XcdMap{3u + shift, 1u << shift, (1u << shift) - 1}; }
+
+__device__ __forceinline__ uint32_t logical_of(uint32_t v, XcdMap map) {
+    return ((v >> map.group_shift) << map.group_shift) + (v & (NXCD - 1)) * map.run +
+           ((v >> 3) & map.mask);
 }
 
-// Grid for n cells in blocks of `block`, padded to a multiple of NXCD << shift.
-inline int64_t grid_blocks(int64_t n, int block, int chunk_shift) {
-    const int64_t g = (n + block - 1) / block;
-    const int64_t q = int64_t(NXCD) << chunk_shift;
-    return std::max<int64_t>(q, (g + q - 1) / q * q);
+__device__ __forceinline__ int64_t logical_block(XcdMap map) { return logical_of(blockIdx.x, map); }
+
+// Virtual blocks of a map over `blocks` blocks (whole groups of NXCD runs).
+__host__ __device__ inline int64_t virtual_blocks(int64_t blocks, XcdMap map) {
+    const int64_t q = int64_t(NXCD) * map.run;
+    return (blocks + q - 1) / q * q;
 }
 
-// log2 of the XCD chunk for n cells from the LBM_FLAG_XCD_CHUNK bits.
-inline int chunk_shift_for(int32_t flags, int64_t n, int block) {
-    const int64_t k = (flags & LBM_FLAG_XCD_CHUNK_MASK) >> LBM_FLAG_XCD_CHUNK_SHIFT;
-    int64_t chunk = k;
-    if (k == 0) chunk = ((n + block - 1) / block + NXCD - 1) / NXCD;  // one eighth each
-    int s = 0;
-    while ((int64_t(1) << (s + 1)) <= chunk && s < 24) ++s;  // largest power of two <= chunk
-    return s;
+// max_nt_bytes of the sweeps of a storage form.
+constexpr size_t sweep_max_nt(int storage) {
+    return storage == LBM_F64 || storage == LBM_F64_SHIFTED ? SIZE_MAX : 0;
+}
+
+// Launch of a sweep over n cells, one workgroup per 256-cell tile: the memory
+// policy and the XCD map.  They follow from the bytes that one step touches
+// (cell_bytes per cell), and the launch flags decide where both choices are
+// good somewhere:
+//  * up to 240 MiB the state stays in the 256 MiB last-level cache: kCached,
+//    and one run of an eighth of the blocks per XCD, so that an XCD finds the
+//    lines that it wrote itself.  The flags are not looked at: nontemporal
+//    accesses and short runs only cost here (246 MB, us a sweep, this form /
+//    nontemporal stores and loads in runs of 1 tile: scaled FP16 over 8-bit
+//    codes 40.1 / 57.3, FP64 over 8-bit codes 38.7 / 49.3; shifted FP32 over
+//    8-bit codes at 204 MB 32.3 / 48.1; FP64 full list at 165 MB 25.9 / 32.7,
+//    at 41 MB 8.0 / 10.6).
+//  * beyond it, runs of as many tiles as the LBM_FLAG_XCD_CHUNK bits say, or,
+//    without them, one run per XCD up to 384 MiB (FP64 full list, 331 MB:
+//    53.4 us against 57.8 with runs of 8 tiles) and then runs of 8 tiles: the
+//    XCDs sweep nearby parts of the list together (DRAM pages) and are evenly
+//    loaded (FP64 full list, 7.5 M cells: 525 us against 554 with an eighth
+//    each; shifted FP32 over codes, 3.6 M: 123 against 137).  Runs of 4 to 64
+//    tiles are within 1 % of it.
+//  * nontemporal stores with LBM_FLAG_NONTEMPORAL, and in FP64 beyond 384 MiB
+//    also without it: there they were faster at every size, ordering and form
+//    (full list 3.3 / 12.7 / 23 / 54 M cells: 223 / 878 / 1,529 / 3,639 us
+//    against 234 / 882 / 1,586 / 3,790; blocked order 8 M box cells 240
+//    against 254), while the narrower storages go either way (shifted FP32
+//    full list: 23 M cells 876 against 926, 12.7 M cells 546 against 530).
+constexpr size_t kCachedBytes = size_t(240) << 20;
+constexpr size_t kContiguousBytes = size_t(384) << 20;
+
+struct SweepLaunch {
+    dim3 grid, block;
+    XcdMap map;
+    int policy;
+};
+
+// max_nt_bytes: largest state that takes nontemporal stores without the flag;
+// block: list cells per workgroup (a multiple of the 256-cell tile).
+inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, size_t max_nt_bytes,
+                                int block = kCodeTile) {
+    const size_t bytes = size_t(n) * cell_bytes;
+    const int64_t blocks = std::max<int64_t>(1, (n + block - 1) / block);
+    const int64_t given = (flags & LBM_FLAG_XCD_CHUNK_MASK) >> LBM_FLAG_XCD_CHUNK_SHIFT;
+    const bool cached = bytes <= kCachedBytes;
+    SweepLaunch l;
+    if (cached || (given == 0 && bytes <= kContiguousBytes)) {
+        l.map = XcdMap{31u, uint32_t((blocks + NXCD - 1) / NXCD), ~0u};
+    } else {
+        const int64_t run = (given ? given : 8) * kCodeTile / block;
+        int shift = 0;
+        while ((int64_t(2) << shift) <= run) ++shift;
+        l.map = map_of_runs(shift);
+    }
+    const bool nt = (flags & LBM_FLAG_NONTEMPORAL) ||
+                    (bytes > kContiguousBytes && bytes <= max_nt_bytes);
+    l.policy = cached ? kCached : nt ? kStreamNT : kStream;
+    l.grid = dim3(unsigned(virtual_blocks(blocks, l.map)));
+    l.block = dim3(unsigned(block));
+    return l;
+}
+
+// Calls f(std::integral_constant<int, policy>).
+template <class F>
+lbm_status with_policy(int policy, F&& f) {
+    switch (policy) {
+    case kCached: return f(std::integral_constant<int, kCached>{});
+    case kStream: return f(std::integral_constant<int, kStream>{});
+    default: return f(std::integral_constant<int, kStreamNT>{});
+    }
 }
 
 }  // namespace lbm

@@ -13,7 +13,7 @@
 //  * workgroups are relabelled so that each XCD (own L2) takes runs of
 //    consecutive list tiles: the neighbours a pull reads are nearby list
 //    entries, so their cache lines are shared within one L2 (run length set
-//    by the LBM_FLAG_XCD_CHUNK bits).
+//    by the LBM_FLAG_XCD_CHUNK bits, or by the size of the state).
 // No MFMA: there is no dense contraction here.
 #include <algorithm>
 
@@ -22,7 +22,7 @@
 
 namespace lbm {
 
-constexpr int kBlock = 256;
+constexpr int kBlock = kCodeTile;
 
 // batch.hip: sweeps with constants from a parameter table (per-segment
 // parameter sets, persistent launch)
@@ -55,15 +55,15 @@ __global__ __launch_bounds__(kBlock) void k_init(typename Storage<ST>::T* __rest
         st<T, typename Storage<ST>::A, false>(f + i * stride + m, static_cast<typename Storage<ST>::A>(e.v[i]));
 }
 
-template <int ST, bool PBB, bool NT>
+template <int ST, bool PBB, int POL>
 __global__ __launch_bounds__(kBlock) void k_trt(const typename Storage<ST>::T* __restrict__ src,
                                                 typename Storage<ST>::T* __restrict__ dst,
                                                 const uint32_t* __restrict__ adj,
                                                 const double* __restrict__ ns, int64_t n,
-                                                int64_t stride, TrtConst c, int chunk_shift) {
-    const int64_t m = logical_block(chunk_shift) * kBlock + threadIdx.x;
+                                                int64_t stride, TrtConst c, XcdMap map) {
+    const int64_t m = logical_block(map) * kBlock + threadIdx.x;
     if (m >= n) return;
-    update_cell<ST, PBB, NT>(src, dst, adj, ns, m, stride, c);
+    update_cell<ST, PBB, POL>(src, dst, adj, ns, m, stride, c);
 }
 
 // ---------------------------------------------------------------------------
@@ -87,34 +87,31 @@ lbm_status launch_init(const lbm_params& p, int64_t n, int64_t stride, void* f, 
     return after_launch();
 }
 
-template <int ST, bool PBB, bool NT>
-lbm_status launch_steps(const TrtConst& c, int chunk_shift, int64_t n, int64_t stride,
-                        const uint32_t* adj, const double* ns, void* fa, void* fb, int n_steps,
-                        hipStream_t s) {
+template <int ST, bool PBB>
+lbm_status launch_steps(const lbm_params& p, int64_t n, int64_t stride, const uint32_t* adj,
+                        const double* ns, void* fa, void* fb, int n_steps, hipStream_t s) {
     using T = typename Storage<ST>::T;
     T* a = static_cast<T*>(fa);
     T* b = static_cast<T*>(fb);
-    const int64_t grid = grid_blocks(n, kBlock, chunk_shift);
-    for (int k = 0; k < n_steps; ++k) {
-        const T* src = (k & 1) ? b : a;
-        T* dst = (k & 1) ? a : b;
-        k_trt<ST, PBB, NT><<<dim3(unsigned(grid)), dim3(kBlock), 0, s>>>(src, dst, adj, ns, n, stride, c,
-                                                                       chunk_shift);
-        if (hipGetLastError() != hipSuccess) return LBM_EHIP;
-    }
-    return LBM_OK;
+    const TrtConst c = make_trt_const(p);
+    const SweepLaunch l = sweep_launch(p.flags, n, 2 * Q * sizeof(T) + (Q - 1) * sizeof(uint32_t),
+                                       sweep_max_nt(ST));
+    return with_policy(l.policy, [&](auto pol) -> lbm_status {
+        for (int k = 0; k < n_steps; ++k) {
+            const T* src = (k & 1) ? b : a;
+            T* dst = (k & 1) ? a : b;
+            k_trt<ST, PBB, pol><<<l.grid, l.block, 0, s>>>(src, dst, adj, ns, n, stride, c, l.map);
+            if (hipGetLastError() != hipSuccess) return LBM_EHIP;
+        }
+        return LBM_OK;
+    });
 }
 
 template <int ST>
 lbm_status dispatch_step(const lbm_params& p, int64_t n, int64_t stride, const uint32_t* adj,
                          const double* ns, void* fa, void* fb, int n_steps, hipStream_t s) {
-    const TrtConst c = make_trt_const(p);
-    const bool nt = (p.flags & LBM_FLAG_NONTEMPORAL) != 0;
-    const int cs = chunk_shift_for(p.flags, n, kBlock);
-    if (ns) return nt ? launch_steps<ST, true, true>(c, cs, n, stride, adj, ns, fa, fb, n_steps, s)
-                      : launch_steps<ST, true, false>(c, cs, n, stride, adj, ns, fa, fb, n_steps, s);
-    return nt ? launch_steps<ST, false, true>(c, cs, n, stride, adj, ns, fa, fb, n_steps, s)
-              : launch_steps<ST, false, false>(c, cs, n, stride, adj, ns, fa, fb, n_steps, s);
+    return ns ? launch_steps<ST, true>(p, n, stride, adj, ns, fa, fb, n_steps, s)
+              : launch_steps<ST, false>(p, n, stride, adj, ns, fa, fb, n_steps, s);
 }
 
 }  // namespace lbm
