@@ -311,6 +311,9 @@ struct XcdMap {
 };
 
 constexpr XcdMap map_of_runs(int shift) { return XcdMap{3u + shift, 1u << shift, (1u << shift) - 1}; }
+constexpr XcdMap map_of_eighths(int64_t blocks) {
+    return XcdMap{31u, uint32_t((blocks + NXCD - 1) / NXCD), ~0u};
+}
 
 __device__ __forceinline__ uint32_t logical_of(uint32_t v, XcdMap map) {
     return ((v >> map.group_shift) << map.group_shift) + (v & (NXCD - 1)) * map.run +
@@ -374,7 +377,7 @@ inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, siz
     const bool cached = bytes <= kCachedBytes;
     SweepLaunch l;
     if (cached || (given == 0 && bytes <= kContiguousBytes)) {
-        l.map = XcdMap{31u, uint32_t((blocks + NXCD - 1) / NXCD), ~0u};
+        l.map = map_of_eighths(blocks);
     } else {
         const int64_t run = (given ? given : 8) * kCodeTile / block;
         int shift = 0;

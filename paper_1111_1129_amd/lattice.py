@@ -84,8 +84,10 @@ def build(flags: torch.Tensor, periodic: int = 0, order: str = "lex", param: int
     N._check("lbm_build_adjacency", st)
     if stride is None:
         stride = aligned_stride(base + nf)
-    if adj is None:
-        adj = torch.zeros((18, stride), dtype=torch.int32, device=dev)
+    if adj is None:  # the library fills this geometry's columns, the others hold 0
+        adj = torch.empty((18, stride), dtype=torch.int32, device=dev)
+        adj[:, :base].zero_()
+        adj[:, base + nf:].zero_()
     assert adj.shape == (18, stride) and adj.dtype == torch.int32 and adj.is_contiguous()
     cell_of = torch.empty(max(nf, 1), dtype=torch.int32, device=dev)
     st, nf2, _ = N.lbm_build_adjacency(g, flags, base, stride, index_of, cell_of, adj, nf, wsb, ws,
