@@ -368,7 +368,9 @@ lbm_status lbm_step_adjoint_c8(const lbm_params* p, int64_t n, int64_t stride,
  *  seg, n_seg  (host) segments, or NULL/0 for one segment [0, n).
  *  totals double [4 * max(n_seg,1)] or NULL.
  *  workspace, ws_bytes  scratch for the reduction (query with workspace NULL);
- *        not needed when totals == NULL.
+ *        not needed when totals == NULL.  Less than the size asked for, down
+ *        to 64 bytes per 256-cell tile of the largest segment (rounded up to a
+ *        multiple of 256 bytes), costs launches.
  *  With LBM_FLAG_CHECK_FINITE in p[0].flags and totals given, the call waits
  *  for the totals and returns LBM_ENONFINITE if any of them is NaN or
  *  infinite (the fields are written either way).
