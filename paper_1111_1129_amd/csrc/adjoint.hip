@@ -29,6 +29,20 @@ constexpr int kAdjBlock = 256;
 // 7.8 M cells 411 / 793 against 393 / 775.
 constexpr size_t kAdjCellBytes = 4 * Q * sizeof(double);
 constexpr size_t kAdjMaxNt = size_t(5) << 28;
+
+// Waves per SIMD that the kernels are built for.  A cell holds 38 gathered and
+// read values in FP64, and the compiler takes 188 registers (two waves) unless
+// told to fit three (168, nothing spilled; four would spill 46).  Three waves
+// up to the same size: 0.35 / 0.85 / 2.0 M cells over 8-bit codes 29.6 / 70.6 /
+// 190.0 us against 32.5 / 76.5 / 192.3 with two, but 7.8 M cells 782 against
+// 771 and with nontemporal stores 823 against 797.
+template <class F>
+lbm_status with_policy_waves(int policy, int64_t n, F&& f) {
+    return with_policy(policy, [&](auto pol) {
+        return size_t(n) * kAdjCellBytes <= kAdjMaxNt ? f(pol, std::integral_constant<int, 3>{})
+                                                      : f(pol, std::integral_constant<int, 2>{});
+    });
+}
 static_assert(kAdjBlock == kCodeTile, "a workgroup of k_adjoint_coded is one code tile");
 
 // The adjoint of one cell m whose 19 slots A (A[0] = m, A[k+1] = the slot it
@@ -40,20 +54,23 @@ __device__ __forceinline__ void adjoint_cell(const double* __restrict__ f_t, con
                                              double* __restrict__ lam_t,
                                              double* __restrict__ grad, int64_t m,
                                              int64_t stride, const TrtConst& c) {
-    double g[Q], mu[Q], fs[Q];
+    double g[Q], mu[Q];
 #pragma unroll
     for (int k = 0; k < Q; ++k) g[k] = f_t[A[k]];
 #pragma unroll
     for (int k = 0; k < Q; ++k) mu[k] = ld_stream<POL>(lam_next + k * stride + m);  // own column, read once
-    trt_collide<double, false>(g, fs, c, 0.0);
     const CellMoments<double> cm = cell_moments(g);
     const double s = PBB ? ns[m] : 0.0;
     if constexpr (PBB) {
-        double acc = mu[0] * (g[0] - fs[0]);
+        // sum of mu_i (g_opp(i) - f*_i), one pair of f* at a time
+        const TrtCell<double> t(cm, c);
+        double acc = mu[0] * (g[0] - t.rest(g[0]));
 #pragma unroll
         for (int k = 0; k < NPAIR; ++k) {
             const int a = 2 * k + 1, b = 2 * k + 2;
-            acc += mu[a] * (g[b] - fs[a]) + mu[b] * (g[a] - fs[b]);
+            double fa, fb;
+            t.pair(k, g[a], g[b], c, fa, fb);
+            acc += mu[a] * (g[b] - fa) + mu[b] * (g[a] - fb);
         }
         if (grad) grad[m] += acc;
     }
@@ -97,8 +114,8 @@ __device__ __forceinline__ void adjoint_cell(const double* __restrict__ f_t, con
     }
 }
 
-template <bool PBB, int POL>
-__global__ __launch_bounds__(kAdjBlock) void k_adjoint(const double* __restrict__ f_t,
+template <bool PBB, int POL, int WAVES>
+__global__ __launch_bounds__(kAdjBlock, WAVES) void k_adjoint(const double* __restrict__ f_t,
                                                        const uint32_t* __restrict__ adj,
                                                        const double* __restrict__ ns,
                                                        const double* __restrict__ lam_next,
@@ -120,8 +137,8 @@ __global__ __launch_bounds__(kAdjBlock) void k_adjoint(const double* __restrict_
 // 8-bit codes of a narrow tile (lbm_narrow_codes), otherwise the 16-bit codes;
 // a tile with escapes reads adj.  The branch is uniform over the workgroup and
 // every form rebuilds the same slots, so the result does not depend on it.
-template <bool PBB, int POL, bool C8>
-__global__ __launch_bounds__(kAdjBlock) void k_adjoint_coded(const double* __restrict__ f_t,
+template <bool PBB, int POL, bool C8, int WAVES>
+__global__ __launch_bounds__(kAdjBlock, WAVES) void k_adjoint_coded(const double* __restrict__ f_t,
                                                              const int8_t* __restrict__ codes8,
                                                              const int16_t* __restrict__ codes,
                                                              const int32_t* __restrict__ tile_rec,
@@ -200,9 +217,9 @@ extern "C" lbm_status lbm_step_adjoint(const lbm_params* p, int64_t n, int64_t s
     const double* f = static_cast<const double*>(f_t);
     // the sweep's launch options: workgroup-to-XCD mapping, memory policy
     const SweepLaunch l = sweep_launch(p->flags, n, kAdjCellBytes, kAdjMaxNt);
-    return with_policy(l.policy, [&](auto pol) {
-        if (ns) k_adjoint<true, pol><<<l.grid, l.block, 0, s>>>(f, adj, ns, lam_next, lam_t, grad_ns, n, stride, c, l.map);
-        else k_adjoint<false, pol><<<l.grid, l.block, 0, s>>>(f, adj, ns, lam_next, lam_t, nullptr, n, stride, c, l.map);
+    return with_policy_waves(l.policy, n, [&](auto pol, auto waves) {
+        if (ns) k_adjoint<true, pol, waves><<<l.grid, l.block, 0, s>>>(f, adj, ns, lam_next, lam_t, grad_ns, n, stride, c, l.map);
+        else k_adjoint<false, pol, waves><<<l.grid, l.block, 0, s>>>(f, adj, ns, lam_next, lam_t, nullptr, n, stride, c, l.map);
         return after_launch();
     });
 }
@@ -224,9 +241,9 @@ lbm_status step_adjoint_coded(const lbm_params* p, int64_t n, int64_t stride,
     const TrtConst c = make_trt_const(*p);
     const double* f = static_cast<const double*>(f_t);
     const SweepLaunch l = sweep_launch(p->flags, n, kAdjCellBytes, kAdjMaxNt);
-    return with_policy(l.policy, [&](auto pol) {
-        if (ns) k_adjoint_coded<true, pol, C8><<<l.grid, l.block, 0, s>>>(f, codes8, codes, tile_records, adj, ns, lam_next, lam_t, grad_ns, n, stride, c, l.map);
-        else k_adjoint_coded<false, pol, C8><<<l.grid, l.block, 0, s>>>(f, codes8, codes, tile_records, adj, ns, lam_next, lam_t, nullptr, n, stride, c, l.map);
+    return with_policy_waves(l.policy, n, [&](auto pol, auto waves) {
+        if (ns) k_adjoint_coded<true, pol, C8, waves><<<l.grid, l.block, 0, s>>>(f, codes8, codes, tile_records, adj, ns, lam_next, lam_t, grad_ns, n, stride, c, l.map);
+        else k_adjoint_coded<false, pol, C8, waves><<<l.grid, l.block, 0, s>>>(f, codes8, codes, tile_records, adj, ns, lam_next, lam_t, nullptr, n, stride, c, l.map);
         return after_launch();
     });
 }

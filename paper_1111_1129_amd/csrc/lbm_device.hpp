@@ -188,30 +188,46 @@ __device__ __forceinline__ CellMoments<A> cell_moments(const A* g) {
     return m;
 }
 
+// The collision of one cell with moments m, one population pair at a time.
+template <class A>
+struct TrtCell {
+    A sp, sm, base;  // base = rho - 3/2 |j|^2
+    CellMoments<A> m;
+    __device__ __forceinline__ TrtCell(const CellMoments<A>& cm, const TrtConst& c)
+        : sp(static_cast<A>(c.sp)), sm(static_cast<A>(c.sm)), m(cm) {
+        const A jj = m.jx * m.jx + m.jy * m.jy + m.jz * m.jz;
+        base = m.rho - A(1.5) * jj;
+    }
+    // rest population: g+ = g0, g- = 0, e+ = w0 (rho - 3/2 |j|^2)
+    __device__ __forceinline__ A rest(A g0) const {
+        return g0 - sp * (g0 - static_cast<A>(W0) * base);
+    }
+    __device__ __forceinline__ void pair(int k, A ga, A gb, const TrtConst& c, A& fa, A& fb) const {
+        const A w = static_cast<A>(pair_weight(k));
+        const A cu = A(PCX[k]) * m.jx + A(PCY[k]) * m.jy + A(PCZ[k]) * m.jz;
+        const A ep = w * (base + A(4.5) * cu * cu);
+        const A em = A(3) * w * cu;
+        const A gp = A(0.5) * (ga + gb);
+        const A gm = A(0.5) * (ga - gb);
+        const A rp = sp * (gp - ep);
+        const A rm = sm * (gm - em);
+        const A F = static_cast<A>(c.F[k]);
+        fa = ga - rp - rm + F;
+        fb = gb - rp + rm - F;
+    }
+};
+
 template <class A, bool PBB>
 __device__ __forceinline__ void trt_collide(const A* g, A* out, const TrtConst& c, A ns) {
-    const CellMoments<A> m = cell_moments(g);
-    const A sp = static_cast<A>(c.sp), sm = static_cast<A>(c.sm);
-    const A jj = m.jx * m.jx + m.jy * m.jy + m.jz * m.jz;
-    const A base = m.rho - A(1.5) * jj;  // rho - 3/2 |j|^2
-    // rest population: g+ = g0, g- = 0, e+ = w0 (rho - 3/2 |j|^2)
-    A f0 = g[0] - sp * (g[0] - static_cast<A>(W0) * base);
+    const TrtCell<A> t(cell_moments(g), c);
+    A f0 = t.rest(g[0]);
     if constexpr (PBB) f0 = (A(1) - ns) * f0 + ns * g[0];
     out[0] = f0;
 #pragma unroll
     for (int k = 0; k < NPAIR; ++k) {
         const int a = 2 * k + 1, b = 2 * k + 2;
-        const A w = static_cast<A>(pair_weight(k));
-        const A cu = A(PCX[k]) * m.jx + A(PCY[k]) * m.jy + A(PCZ[k]) * m.jz;
-        const A ep = w * (base + A(4.5) * cu * cu);
-        const A em = A(3) * w * cu;
-        const A gp = A(0.5) * (g[a] + g[b]);
-        const A gm = A(0.5) * (g[a] - g[b]);
-        const A rp = sp * (gp - ep);
-        const A rm = sm * (gm - em);
-        const A F = static_cast<A>(c.F[k]);
-        A fa = g[a] - rp - rm + F;
-        A fb = g[b] - rp + rm - F;
+        A fa, fb;
+        t.pair(k, g[a], g[b], c, fa, fb);
         if constexpr (PBB) {
             fa = (A(1) - ns) * fa + ns * g[b];
             fb = (A(1) - ns) * fb + ns * g[a];
