@@ -33,9 +33,9 @@
 // and divides by multiplication (box indices fit 31 bits).  Every wave walks
 // its own run of positions, 16 rows at a time with all 16 flag loads in flight
 // before the first ballot, and needs no barrier.  us for count / emit, before
-// -> now: lexicographic, 75 M box cells 95 / 172 -> 27 / 97 (emit moves 0.5 GB,
+// -> now: lexicographic, 75 M box cells 95 / 172 -> 24 / 97 (emit moves 0.5 GB,
 // 5.2 TB/s); Hilbert curve over a 500 x 100 x 100 box, 134 M positions 718 /
-// 758 -> 73 / 90.
+// 758 -> 48 / 58.
 #include <algorithm>
 
 #include "lbm_device.hpp"
@@ -49,7 +49,7 @@ constexpr int kRow = 64;                     // positions of one wave load
 constexpr int kRows = 16;                    // rows of a unit, in flight together
 constexpr int kUnit = kRows * kRow;          // 1024 positions
 constexpr int kTileUnits = 4;                // units of a tile (4096 positions)
-constexpr int64_t kMaxGroups = 16384;        // waves of a walk
+constexpr int64_t kMaxGroups = 32768;        // waves of a walk
 constexpr int kScanThreads = 1024;
 constexpr uint64_t kMaxPositions = uint64_t(1) << 34;
 
@@ -221,9 +221,9 @@ __device__ __forceinline__ Orient orientation(Vec3 gray, int levels) {
 
 // Walk over the positions of one order, in tiles of 4096.  tile() is called
 // with the index of a tile (uniform over the wave) and returns 0, or how many
-// tiles from this one on (1, 8 or 64, never past a multiple of that) hold no
-// cell of the box.  row() is called for a row of the tile (uniform) and cell()
-// gives the box cell (linear index) at a lane of it, -1 for a gap.
+// tiles from this one on are known to hold no cell of the box.  row() is called
+// for a row of the tile (uniform) and cell() gives the box cell (linear index)
+// at a lane of it, -1 for a gap.
 template <int ORDER> struct Walk;
 
 template <> struct Walk<LBM_ORDER_LEX> {
@@ -296,8 +296,25 @@ template <> struct Walk<LBM_ORDER_BLOCKED> {
     }
 };
 
-// Tiles from t on, of a curve whose aligned cubes are aligned runs of
-// positions, that lie outside the box; c is any cell of tile t.
+// A curve's aligned cubes are aligned runs of positions.  `digits` is the
+// number of binary digits of a tile's coordinates; the first two, decoded by
+// themselves, already show most of the tiles outside a box that is much
+// smaller than its cube.  decode(p, n): the cube of n leading digits p.
+// Returns the tiles left in that cube if it lies outside the box, else 0.
+template <class F>
+__device__ __forceinline__ uint32_t coarse_tiles_outside(const KeySpace& ks, uint32_t t, int digits,
+                                                         F&& decode) {
+    if (digits <= 2) return 0;
+    const int rest = digits - 2;
+    const Vec3 c = decode(t >> (3 * rest), 2);
+    const bool out = (c.x << (rest + 4)) >= ks.nx || (c.y << (rest + 4)) >= ks.ny ||
+                     (c.z << (rest + 4)) >= ks.nz;
+    const uint32_t run = 1u << (3 * rest);
+    return out ? run - (t & (run - 1)) : 0u;
+}
+
+// The same for the cubes of 64, 8 and 1 tiles that begin at t; c is any cell of
+// tile t.
 __device__ __forceinline__ uint32_t tiles_outside(const KeySpace& ks, uint32_t t, Vec3 c) {
     for (int s = 2; s >= 0; --s) {
         const uint32_t run = 1u << (3 * s), edge = 16u << s;
@@ -311,6 +328,10 @@ template <int GB> struct ZWalk {
     Vec3 lane_c, tile_c, row_c;
     __device__ explicit ZWalk(int lane) : lane_c(deinterleave<GB>(uint64_t(lane), 2 / GB)) {}
     __device__ __forceinline__ uint32_t tile(const KeySpace& ks, uint32_t t) {
+        const uint32_t skip = coarse_tiles_outside(
+            ks, t, ks.groups * GB - 4,
+            [](uint32_t p, int n) { return deinterleave<GB>(p, n / GB); });
+        if (skip) return skip;
         tile_c = deinterleave<GB>(t, ks.groups - 4 / GB);
         tile_c = Vec3{tile_c.x << 4, tile_c.y << 4, tile_c.z << 4};
         return tiles_outside(ks, t, tile_c);
@@ -341,9 +362,12 @@ template <> struct Walk<LBM_ORDER_HILBERT> {
         t = tile;
         if (ks.groups < 4) return 0;
         Vec3 g;
+        uint32_t skip = coarse_tiles_outside(
+            ks, t, ks.groups - 4, [&](uint32_t p, int n) { return hilbert_digits(p, n, 0u, g); });
+        if (skip) return skip;
         tile_c = hilbert_digits(t, ks.groups - 4, 0u, g);
         tile_c = Vec3{tile_c.x << 4, tile_c.y << 4, tile_c.z << 4};
-        const uint32_t skip = tiles_outside(ks, t, tile_c);
+        skip = tiles_outside(ks, t, tile_c);
         if (skip == 0) tile_o = orientation(g, ks.groups - 4);
         return skip;
     }
@@ -441,17 +465,31 @@ __global__ __launch_bounds__(kWalkBlock) void k_count(KeySpace ks, const uint8_t
     if (lane == 0) group_count[g] = mine;
 }
 
-// Exclusive scan of n <= kMaxGroups counts in place, total written to *total.
+// Exclusive scan of n <= kMaxGroups counts in place (room for a multiple of 4),
+// total written to *total.  One workgroup: each thread takes a run of counts,
+// four to a load.
 __global__ __launch_bounds__(kScanThreads) void k_scan(uint32_t* __restrict__ v, int n,
                                                        int64_t* __restrict__ total) {
-    constexpr int kPer = int(kMaxGroups) / kScanThreads;
+    constexpr int kMaxQuads = int(kMaxGroups) / kScanThreads / 4;
     __shared__ uint32_t wave_tot[kScanThreads / 64];
     const int tid = threadIdx.x;
-    uint32_t c[kPer], local = 0;
+    const int quads = (n + 4 * kScanThreads - 1) / (4 * kScanThreads);  // of each thread
+    uint4* const q = reinterpret_cast<uint4*>(v) + int64_t(tid) * quads;
+    uint4 c[kMaxQuads];
+    uint32_t local = 0;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) c[i] = tid * kPer + i < n ? v[tid * kPer + i] : 0u;
+    for (int i = 0; i < kMaxQuads; ++i) {
+        c[i] = uint4{0u, 0u, 0u, 0u};
+        const int at = 4 * (tid * quads + i);
+        if (i < quads && at < n) {
+            c[i] = q[i];
+            if (at + 1 >= n) c[i].y = 0u;
+            if (at + 2 >= n) c[i].z = 0u;
+            if (at + 3 >= n) c[i].w = 0u;
+        }
+    }
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) local += c[i];
+    for (int i = 0; i < kMaxQuads; ++i) local += c[i].x + c[i].y + c[i].z + c[i].w;
     // inclusive scan of `local` across the workgroup (a box has < 2^31 cells)
     const int lane = tid & 63, wave = tid >> 6;
     uint32_t x = local;
@@ -464,9 +502,16 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(uint32_t* __restrict__ v,
     uint32_t run = x - local;  // exclusive prefix of this thread's counts
     for (int w = 0; w < wave; ++w) run += wave_tot[w];
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        if (tid * kPer + i < n) v[tid * kPer + i] = run;
-        run += c[i];
+    for (int i = 0; i < kMaxQuads; ++i) {
+        if (i < quads && 4 * (tid * quads + i) < n) {
+            uint4 o;
+            o.x = run;
+            o.y = o.x + c[i].x;
+            o.z = o.y + c[i].y;
+            o.w = o.z + c[i].z;
+            q[i] = o;
+        }
+        run += c[i].x + c[i].y + c[i].z + c[i].w;
     }
     if (tid == kScanThreads - 1) *total = int64_t(run);
 }

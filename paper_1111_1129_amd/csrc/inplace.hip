@@ -156,8 +156,12 @@ lbm_status launch_inplace(const lbm_params& p, int64_t n, int64_t stride, const 
     using T = typename Storage<ST>::T;
     T* f = static_cast<T*>(fv);
     const TrtConst c = make_trt_const(p);
+    // nontemporal stores without the flag in every storage: the local step
+    // writes whole lines that it has just read (shifted FP32 12.7 / 30.6 M
+    // cells 405 / 999 us a sweep against 427 / 1,025 with plain stores, scaled
+    // FP16 232 / 598 against 248 / 616), the gather-scatter step does not mind
     const SweepLaunch l = sweep_launch(p.flags, n, Q * sizeof(T) + (Q - 1) * (codes8 ? 1 : codes ? 2 : 4),
-                                       sweep_max_nt(ST));
+                                       SIZE_MAX);
     return with_policy(l.policy, [&](auto pol) -> lbm_status {
         for (int k = 0; k < n_steps; ++k) {
             if (((phase + k) & 1) == 0) {
