@@ -12,8 +12,8 @@
 // reduces, by wave shifts rather than a tree of barriers, and the second pass
 // has few partials.  All segments that fit one argument block share the two
 // launches.  us before -> now: totals of 33.9 M cells FP64 / shifted FP32 /
-// scaled FP16 1,707 / 1,251 / 1,008 -> 1,390 / 916 / 671 (5.5 TB/s), with fields
-// of 7.5 M cells FP64 451 -> 400.
+// scaled FP16 1,707 / 1,251 / 1,008 -> 1,392 / 936 / 680 (5.4 TB/s), with fields
+// of 7.5 M / 0.95 / 0.41 M cells FP64 451 / 57.7 / 27.7 -> 396 / 52.6 / 24.3.
 #include <algorithm>
 #include <mutex>
 
@@ -41,45 +41,58 @@ __device__ __forceinline__ DD dd_add(DD a, DD b) {
     return DD{hi, e - (hi - s)};
 }
 
-// A value of another lane of the wave; 0 where the pattern has none.
+// A value of another lane of the wave, by a pattern that names one for each.
 template <int CTRL>
-__device__ __forceinline__ double lane_move(double v) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0u, uint32_t(u), CTRL, 0xf, 0xf, false);
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0u, uint32_t(u >> 32), CTRL, 0xf, 0xf, false);
-    return __builtin_bit_cast(double, uint64_t(hi) << 32 | lo);
+__device__ __forceinline__ DD lane_move(DD v) {
+    DD r;
+    const uint64_t h = __builtin_bit_cast(uint64_t, v.hi), l = __builtin_bit_cast(uint64_t, v.lo);
+    const uint32_t w[4] = {
+        uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(h)), CTRL, 0xf, 0xf, true)),
+        uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(h >> 32)), CTRL, 0xf, 0xf, true)),
+        uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(l)), CTRL, 0xf, 0xf, true)),
+        uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(l >> 32)), CTRL, 0xf, 0xf, true))};
+    r.hi = __builtin_bit_cast(double, uint64_t(w[1]) << 32 | w[0]);
+    r.lo = __builtin_bit_cast(double, uint64_t(w[3]) << 32 | w[2]);
+    return r;
 }
 
-template <int CTRL>
-__device__ __forceinline__ void dd_add_moved(DD& v) {
-    v = dd_add(v, DD{lane_move<CTRL>(v.hi), lane_move<CTRL>(v.lo)});
+// The quantity that a lane ends up with in block_reduce4.
+__device__ __forceinline__ int quantity_of(int lane) { return (lane & 1) << 1 | ((lane >> 1) & 1); }
+
+// Sum over the 4 lanes of a row of 16 that hold the same quantity, in each.
+__device__ __forceinline__ DD row_sum(DD v) {
+    v = dd_add(v, lane_move<0x128>(v));  // rotate by 8
+    return dd_add(v, lane_move<0x124>(v));  // by 4
 }
 
-// Fixed-shape reduction of 4 DD values over a workgroup of WAVES waves: within
-// each wave (the sum ends in lane 63), then the wave sums in order.  The
-// result is valid in thread 0.
+// Fixed-shape reduction of 4 DD values over a workgroup of WAVES waves.  Lanes
+// share the work: a pair of lanes splits the four quantities, a pair of pairs
+// splits them again, and each lane then sums one of them over its row of 16
+// (5 additions instead of 16); the rows' sums meet in LDS, and the first wave
+// adds them up.  Threads 0 to 3 return quantity_of(thread).
 template <int WAVES>
-__device__ __forceinline__ void block_reduce4(DD v[4]) {
-    __shared__ DD wave_sum[WAVES][4];
-    const int wave = int(threadIdx.x) >> 6, lane = int(threadIdx.x) & 63;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        dd_add_moved<0xB1>(v[q]);   // neighbours, pairs, halves of 8, halves of a row of 16
-        dd_add_moved<0x4E>(v[q]);
-        dd_add_moved<0x141>(v[q]);
-        dd_add_moved<0x140>(v[q]);
-        dd_add_moved<0x142>(v[q]);  // lane 15 of a row to the next row, lane 31 to the upper half
-        dd_add_moved<0x143>(v[q]);
-        if (lane == 63) wave_sum[wave][q] = v[q];
-    }
+__device__ __forceinline__ DD block_reduce4(const DD v[4]) {
+    constexpr int kParts = 4 * WAVES;  // rows of 16 lanes
+    __shared__ DD row_part[kParts][4];
+    const int lane = int(threadIdx.x) & 63;
+    const bool odd = lane & 1, upper = lane & 2;
+    DD a = odd ? v[2] : v[0], b = odd ? v[3] : v[1];
+    a = dd_add(a, lane_move<0xB1>(odd ? v[0] : v[2]));
+    b = dd_add(b, lane_move<0xB1>(odd ? v[1] : v[3]));
+    DD one = dd_add(upper ? b : a, lane_move<0x4E>(upper ? a : b));
+    one = row_sum(one);
+    if ((lane & 15) < 4) row_part[threadIdx.x >> 4][lane & 3] = one;
     __syncthreads();
-    if (threadIdx.x == 0) {
+    DD sum{0.0, 0.0};
+    if (threadIdx.x < 64) {
+        // lane 4 e + j: parts e, e + 16, ... of the quantity in place j
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            v[q] = wave_sum[0][q];
-            for (int w = 1; w < WAVES; ++w) v[q] = dd_add(v[q], wave_sum[w][q]);
-        }
+        for (int e = 0; e < kParts; e += 16) sum = dd_add(sum, row_part[e + (lane >> 2)][lane & 3]);
+        sum = row_sum(sum);
+        sum = dd_add(sum, DD{__shfl_xor(sum.hi, 16), __shfl_xor(sum.lo, 16)});
+        sum = dd_add(sum, DD{__shfl_xor(sum.hi, 32), __shfl_xor(sum.lo, 32)});
     }
+    return sum;
 }
 
 // One segment of a launch: its cells, its workgroups and half its force.
@@ -89,20 +102,23 @@ struct MomSeg {
     int32_t first, blocks;
 };
 
+// The segments of a launch, up to SEGS of them; a launch of one segment is
+// written without the 3 KB of arguments that many take.
+template <int SEGS>
 struct MomChunk {
     int32_t count;
     int32_t per_block;  // cells of a workgroup
-    MomSeg s[kMomSegs];
+    MomSeg s[SEGS];
 };
-static_assert(sizeof(MomChunk) < 3800, "fits the kernel arguments beside the pointers");
+static_assert(sizeof(MomChunk<kMomSegs>) < 3800, "fits the kernel arguments beside the pointers");
 
-template <int ST>
+template <int ST, int SEGS>
 __global__ __launch_bounds__(kMomBlock) void k_moments(const typename Storage<ST>::T* __restrict__ f,
                                                        const uint32_t* __restrict__ adj,
                                                        int64_t stride, double* __restrict__ rho,
                                                        double* __restrict__ u, int64_t ld,
                                                        double* __restrict__ partial,
-                                                       MomChunk chunk) {
+                                                       MomChunk<SEGS> chunk) {
     const int32_t block = int32_t(blockIdx.x);
     int lo = 0, hi = chunk.count - 1;  // the segment of this workgroup
     while (lo < hi) {
@@ -144,23 +160,22 @@ __global__ __launch_bounds__(kMomBlock) void k_moments(const typename Storage<ST
         v[3] = dd_add(v[3], DD{uz, 0.0});
     }
     if (!partial) return;
-    block_reduce4<kMomBlock / 64>(v);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            partial[(int64_t(block) * 4 + q) * 2] = v[q].hi;
-            partial[(int64_t(block) * 4 + q) * 2 + 1] = v[q].lo;
-        }
+    const DD sum = block_reduce4<kMomBlock / 64>(v);
+    if (threadIdx.x < 4) {
+        double* p = partial + (int64_t(block) * 4 + quantity_of(int(threadIdx.x))) * 2;
+        p[0] = sum.hi;
+        p[1] = sum.lo;
     }
 }
 
 // One workgroup per segment of the launch: totals (4 values) and/or the
 // objective (the x total divided by the cell count).
+template <int SEGS>
 __global__ __launch_bounds__(kRedThreads) void k_reduce_partials(const double* __restrict__ partial,
                                                                  double* __restrict__ totals,
                                                                  double* __restrict__ objective,
-                                                                 MomChunk chunk) {
-    const MomSeg& seg = chunk.s[blockIdx.x];
+                                                                 MomChunk<SEGS> chunk) {
+    const MomSeg& seg = chunk.s[SEGS > 1 ? blockIdx.x : 0];
     DD v[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
     // thread t sums partials t, t + T, t + 2T, ... in order
     for (int64_t b = threadIdx.x; b < seg.blocks; b += kRedThreads) {
@@ -168,13 +183,12 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_partials(const double* _
 #pragma unroll
         for (int q = 0; q < 4; ++q) v[q] = dd_add(v[q], DD{p[2 * q], p[2 * q + 1]});
     }
-    block_reduce4<kRedThreads / 64>(v);
-    if (threadIdx.x == 0) {
-        if (totals) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) totals[4 * blockIdx.x + q] = v[q].hi + v[q].lo;
-        }
-        if (objective) objective[blockIdx.x] = (v[1].hi + v[1].lo) / double(seg.n);
+    const DD sum = block_reduce4<kRedThreads / 64>(v);
+    if (threadIdx.x < 4) {
+        const int q = quantity_of(int(threadIdx.x));
+        const double total = sum.hi + sum.lo;
+        if (totals) totals[4 * blockIdx.x + q] = total;
+        if (objective && q == 1) objective[blockIdx.x] = total / double(seg.n);
     }
 }
 
@@ -182,27 +196,22 @@ inline int64_t seg_tiles(int64_t n) { return std::max<int64_t>(1, (n + kMomBlock
 
 // Launches all segments; `parts` is the number of partials (64 bytes each) that
 // `partial` holds, at least min(target, tiles) of the largest segment.
-template <int ST>
-lbm_status launch_moments(const lbm_params* p, int64_t n, int64_t stride, const uint32_t* adj,
-                          const void* f, double* rho, double* u, const lbm_segment* seg,
-                          int32_t n_seg, double* totals, double* objective, double* partial,
-                          int64_t parts, int64_t target, hipStream_t s) {
-    lbm_segment whole{0, n, 0, 0};
-    if (!seg || n_seg == 0) {
-        seg = &whole;
-        n_seg = 1;
-    }
+template <int ST, int SEGS>
+lbm_status launch_segments(const lbm_params* p, int64_t n, int64_t stride, const uint32_t* adj,
+                           const void* f, double* rho, double* u, const lbm_segment* seg,
+                           int32_t n_seg, double* totals, double* objective, double* partial,
+                           int64_t parts, int64_t target, hipStream_t s) {
     const bool reduce = totals || objective;
     int64_t all_tiles = 0;
     for (int32_t k = 0; k < n_seg; ++k) all_tiles += seg_tiles(seg[k].n);
     const int64_t per = (all_tiles + target - 1) / target;  // tiles of a workgroup
     for (int32_t k0 = 0; k0 < n_seg;) {
-        MomChunk ch;
+        MomChunk<SEGS> ch;
         ch.count = 0;
         ch.per_block = int32_t(per * kMomBlock);
         int64_t blocks = 0;
         int32_t k = k0;
-        for (; k < n_seg && ch.count < kMomSegs; ++k) {
+        for (; k < n_seg && ch.count < SEGS; ++k) {
             const int64_t b = (seg_tiles(seg[k].n) + per - 1) / per;
             if (ch.count > 0 && reduce && blocks + b > parts) break;
             const lbm_params& pk = p[seg[k].param_index];
@@ -214,13 +223,13 @@ lbm_status launch_moments(const lbm_params* p, int64_t n, int64_t stride, const 
             t.blocks = int32_t(b);
             blocks += b;
         }
-        k_moments<ST><<<dim3(unsigned(blocks)), dim3(kMomBlock), 0, s>>>(
+        k_moments<ST, SEGS><<<dim3(unsigned(blocks)), dim3(kMomBlock), 0, s>>>(
             static_cast<const typename Storage<ST>::T*>(f), adj, stride, rho, u, n,
             reduce ? partial : nullptr, ch);
         if (hipGetLastError() != hipSuccess) return LBM_EHIP;
         if (reduce) {
             // launches run one after another on the stream, so they reuse the partials
-            k_reduce_partials<<<dim3(unsigned(ch.count)), dim3(kRedThreads), 0, s>>>(
+            k_reduce_partials<SEGS><<<dim3(unsigned(ch.count)), dim3(kRedThreads), 0, s>>>(
                 partial, totals ? totals + 4 * int64_t(k0) : nullptr,
                 objective ? objective + k0 : nullptr, ch);
             if (hipGetLastError() != hipSuccess) return LBM_EHIP;
@@ -228,6 +237,22 @@ lbm_status launch_moments(const lbm_params* p, int64_t n, int64_t stride, const 
         k0 = k;
     }
     return LBM_OK;
+}
+
+template <int ST>
+lbm_status launch_moments(const lbm_params* p, int64_t n, int64_t stride, const uint32_t* adj,
+                          const void* f, double* rho, double* u, const lbm_segment* seg,
+                          int32_t n_seg, double* totals, double* objective, double* partial,
+                          int64_t parts, int64_t target, hipStream_t s) {
+    const lbm_segment whole{0, n, 0, 0};
+    if (!seg || n_seg == 0) {
+        seg = &whole;
+        n_seg = 1;
+    }
+    return n_seg == 1 ? launch_segments<ST, 1>(p, n, stride, adj, f, rho, u, seg, 1, totals,
+                                               objective, partial, parts, target, s)
+                      : launch_segments<ST, kMomSegs>(p, n, stride, adj, f, rho, u, seg, n_seg, totals,
+                                                      objective, partial, parts, target, s);
 }
 
 // Reads `count` totals back in fixed-size pieces (no allocation) after the
