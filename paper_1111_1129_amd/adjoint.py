@@ -15,11 +15,51 @@ Backward, two schedules over the same kernels (bitwise the same gradient):
 """
 from __future__ import annotations
 
+import ctypes as C
+
 import torch
 
 from . import _native as N
 from .checkpointing import Revolve
-from .lattice import Compressed, Lattice, compress, init, narrow, objective, step_c8
+from .lattice import Compressed, Lattice, compress, init, narrow, objective
+
+
+class _Steps:
+    """Sweeps and adjoint steps of one lattice over its codes, on the stream
+    that is current when this is made.  What does not change from call to call
+    is resolved once: a small box is stepped as fast as its calls are issued."""
+
+    def __init__(self, lat: Lattice, prm, comp: Compressed, ns: torch.Tensor | None):
+        lib = N.load()
+        self.keep = (lat, prm, comp, ns)
+        head = (C.byref(prm), lat.n_fluid, lat.stride, comp.codes8.data_ptr(),
+                comp.codes.data_ptr(), comp.tile_records.data_ptr(), lat.adj.data_ptr())
+        ns_ptr, stream = N._ptr(ns), N._stream()
+        step, adjoint = lib.lbm_step_c8, lib.lbm_step_adjoint_c8
+
+        def sweeps(src: torch.Tensor, dst: torch.Tensor, k: int = 1):
+            """k sweeps from src, alternating between dst and src (dst first)."""
+            rc = step(*head, ns_ptr, src.data_ptr(), dst.data_ptr(), k, stream)
+            if rc:
+                N._check("lbm_step_c8", rc)
+
+        def adjoint_step(f_t, lam_next, lam_t, grad):
+            rc = adjoint(*head, f_t.data_ptr(), ns_ptr, lam_next.data_ptr(), lam_t.data_ptr(),
+                         grad.data_ptr(), stream)
+            if rc:
+                N._check("lbm_step_adjoint_c8", rc)
+
+        self.sweeps, self.adjoint_step = sweeps, adjoint_step
+
+    def advance(self, src, a, b, k: int):
+        """State k sweeps after src, src itself left as it is: the first sweep
+        reads it, the others alternate between a and b.  Returns (the array
+        that holds the result, the other one); b may be None if k is 1."""
+        self.sweeps(src, a)
+        if k == 1:
+            return a, b
+        self.sweeps(a, b, k - 1)
+        return (b, a) if (k - 1) % 2 else (a, b)
 
 
 def codes_of(lat: Lattice, comp: Compressed | None) -> Compressed:
@@ -37,15 +77,32 @@ def forward_states(lat: Lattice, prm, ns: torch.Tensor, T: int, k: int,
     full list, fewer bytes)."""
     comp = codes_of(lat, comp)
     st = init(lat, prm, ns=ns)
+    steps = _Steps(lat, prm, comp, ns)
     ckpts = []
+    cur, spare = st.f, st.g
     t = 0
     while t < T:
-        ckpts.append(st.f.clone())
+        # the array that holds the state is the checkpoint (nothing writes it
+        # again); the segment goes on in two others
+        ckpts.append(cur)
         n = min(k, T - t)
-        step_c8(st, comp, n)
+        a = torch.empty_like(cur) if spare is None else spare
+        b = torch.empty_like(cur) if n > 1 else None
+        cur, spare = steps.advance(cur, a, b, n)
         t += n
+    st.f, st.g = cur, torch.empty_like(cur) if spare is None else spare
+    st.steps += T
     J = objective(st)[0]  # mean x velocity, formed in the library (lbm_objective)
     return J, ckpts, st
+
+
+def _as_state(ckpt: torch.Tensor, like: torch.Tensor) -> torch.Tensor:
+    """A caller's checkpoint as the kernels read it: itself, or a copy laid out
+    like `like` if it is kept elsewhere or in another form."""
+    if (ckpt.shape == like.shape and ckpt.dtype == like.dtype and ckpt.device == like.device
+            and ckpt.is_contiguous()):
+        return ckpt
+    return torch.empty_like(like).copy_(ckpt)
 
 
 def adjoint_gradient(lat: Lattice, prm, ns: torch.Tensor, T: int, k: int, ckpts=None,
@@ -62,20 +119,17 @@ def adjoint_gradient(lat: Lattice, prm, ns: torch.Tensor, T: int, k: int, ckpts=
     lam_prev = torch.empty_like(lam)
     grad = torch.zeros(S, dtype=torch.float64, device=dev)
     N._check("lbm_step_adjoint", N.lbm_step_adjoint(prm, n, S, lat.adj, None, ns, None, lam, None))
-    buf = [torch.empty_like(ckpts[0]) for _ in range(k)]
-    nseg = len(ckpts)
-    for s in range(nseg - 1, -1, -1):
+    steps = _Steps(lat, prm, comp, ns)
+    # states of a segment after its first, which is the checkpoint itself
+    buf = [torch.empty_like(lam) for _ in range(min(k, T) - 1)] if ckpts else []
+    for s in range(len(ckpts) - 1, -1, -1):
         t0 = s * k
-        t1 = min(t0 + k, T)
-        buf[0].copy_(ckpts[s])
-        for j in range(1, t1 - t0):
-            st = N.lbm_step_c8(prm, n, S, comp.codes8, comp.codes, comp.tile_records, lat.adj,
-                               ns, buf[j - 1], buf[j], 1)
-            N._check("lbm_step_c8", st)
-        for t in range(t1 - 1, t0 - 1, -1):
-            rc = N.lbm_step_adjoint_c8(prm, n, S, comp.codes8, comp.codes, comp.tile_records,
-                                       lat.adj, buf[t - t0], ns, lam, lam_prev, grad)
-            N._check("lbm_step_adjoint_c8", rc)
+        n_seg = min(t0 + k, T) - t0
+        states = [_as_state(ckpts[s], lam)] + buf[:n_seg - 1]
+        for j in range(1, n_seg):
+            steps.sweeps(states[j - 1], states[j])
+        for f_t in reversed(states):
+            steps.adjoint_step(f_t, lam, lam_prev, grad)
             lam, lam_prev = lam_prev, lam
     return grad
 
@@ -101,25 +155,17 @@ def adjoint_gradient_revolve(lat: Lattice, prm, ns: torch.Tensor, T: int, snapsh
     N._check("lbm_step_adjoint", N.lbm_step_adjoint(prm, n, S, lat.adj, None, ns, None, lam, None))
     lams = [lam, lam_prev]
     swept = [0]
-
-    def sweeps(src, dst, k):
-        rc = N.lbm_step_c8(prm, n, S, comp.codes8, comp.codes, comp.tile_records, lat.adj, ns,
-                           src, dst, k)
-        N._check("lbm_step_c8", rc)
+    steps = _Steps(lat, prm, comp, ns)
 
     def advance(src, dst, t, k):
-        # no copy: the first sweep reads slot src, the rest alternate between
-        # slot dst and the spare array so that the last one writes slot dst
+        # no copy: the sweeps after the first alternate between slot dst and
+        # the spare array so that the last one writes slot dst
         a, b = (slots[dst], spare) if (k - 1) % 2 == 0 else (spare, slots[dst])
-        sweeps(slots[src], a, 1)
-        if k > 1:
-            sweeps(a, b, k - 1)  # k - 1 sweeps from a end in b if odd, in a if even
+        steps.advance(slots[src], a, b, k)
         swept[0] += k
 
     def adjoint(slot, t):
-        rc = N.lbm_step_adjoint_c8(prm, n, S, comp.codes8, comp.codes, comp.tile_records, lat.adj,
-                                   slots[slot], ns, lams[0], lams[1], grad)
-        N._check("lbm_step_adjoint_c8", rc)
+        steps.adjoint_step(slots[slot], lams[0], lams[1], grad)
         lams.reverse()
 
     plan.run(advance, adjoint)
@@ -143,12 +189,13 @@ class PermeabilityFn(torch.autograd.Function):
         snapshots = snapshots_arg[0] if snapshots_arg else None
         ctx.n_inputs = 5 + len(snapshots_arg)
         nsd = ns.detach().contiguous()
+        comp = codes_of(lat, None)
         if snapshots is None:
-            J, ckpts, _ = forward_states(lat, prm, nsd, T, k)
+            J, ckpts, _ = forward_states(lat, prm, nsd, T, k, comp)
         else:
-            J, ckpts = forward_states(lat, prm, nsd, T, max(T, 1))[0], None
+            J, ckpts = forward_states(lat, prm, nsd, T, max(T, 1), comp)[0], None
         ctx.lat, ctx.prm, ctx.T, ctx.k, ctx.snapshots = lat, prm, T, k, snapshots
-        ctx.ckpts = ckpts
+        ctx.ckpts, ctx.comp = ckpts, comp
         ctx.save_for_backward(nsd)
         return J
 
@@ -156,8 +203,8 @@ class PermeabilityFn(torch.autograd.Function):
     def backward(ctx, gJ):
         (ns,) = ctx.saved_tensors
         if ctx.snapshots is None:
-            grad = adjoint_gradient(ctx.lat, ctx.prm, ns, ctx.T, ctx.k, ctx.ckpts)
+            grad = adjoint_gradient(ctx.lat, ctx.prm, ns, ctx.T, ctx.k, ctx.ckpts, ctx.comp)
         else:
-            grad = adjoint_gradient_revolve(ctx.lat, ctx.prm, ns, ctx.T, ctx.snapshots)
+            grad = adjoint_gradient_revolve(ctx.lat, ctx.prm, ns, ctx.T, ctx.snapshots, ctx.comp)
         ctx.ckpts = None
         return (grad * gJ,) + (None,) * (ctx.n_inputs - 1)
