@@ -516,26 +516,71 @@ __global__ __launch_bounds__(kScanThreads) void k_scan(uint32_t* __restrict__ v,
     if (tid == kScanThreads - 1) *total = int64_t(run);
 }
 
-template <int ORDER>
+// Lexicographic order: the fluid cells among 32 consecutive box cells and the
+// rank of the first of them.  A table of these holds all that index_of does in
+// a sixteenth of the bytes.  Entry w + 1 covers cells [32 w, 32 w + 32); the
+// first and the last kRankGuard entries are empty.
+struct RankWord {
+    uint32_t mask, rank;
+};
+constexpr int64_t kRankGuard = 2;
+
+inline int64_t rank_words(int64_t units) { return 1 + units * (kUnit / 32) + kRankGuard; }
+
+// Smallest box for the rank words: below it index_of stays in the last-level
+// cache between the two kernels, and reading it costs less than a second pass
+// over the flags (whole call, index / words: 320^3 273 / 281 us and, with
+// porosity 0.8, 426 / 452; 384^3 634 / 460 and 1,084 / 765).  The words fit in
+// the index: a quarter of it, and a unit's worth and the guards beyond that.
+constexpr int64_t kTableBox = int64_t(40) << 20;
+static_assert((kTableBox / 32 + kUnit / 32 + 1 + kRankGuard) * sizeof(RankWord) <=
+              kTableBox * sizeof(int32_t), "rank words fit in the index");
+
+// Which of its results a k_emit launch writes: the list and the index, the list
+// and the rank words, or the index.
+enum EmitPart { kEmitAll = 0, kEmitList = 1, kEmitIndex = 2 };
+
+template <int ORDER, int PART>
 __global__ __launch_bounds__(kWalkBlock) void k_emit(KeySpace ks, const uint8_t* __restrict__ flag,
                                                      uint32_t units, uint32_t per, uint32_t groups,
                                                      const uint32_t* __restrict__ group_offset,
                                                      int32_t* __restrict__ index_of,
-                                                     int32_t* __restrict__ cell_of) {
+                                                     int32_t* __restrict__ cell_of,
+                                                     RankWord* __restrict__ table) {
     const uint32_t g = wave_group();
+    if (PART == kEmitList && g == 0 && threadIdx.x <= kRankGuard)
+        table[threadIdx.x == 0 ? 0 : int64_t(units) * (kUnit / 32) + threadIdx.x] = RankWord{0u, 0u};
     if (g >= groups) return;
     const int lane = int(threadIdx.x) & 63;
     uint32_t r = group_offset[g];
+    uint32_t u = g * per;  // lexicographic order: the unit at hand (none is passed over)
     walk_units<ORDER>(ks, flag, g * per, min(units, (g + 1) * per), lane,
                       [&](const int32_t* lin, const uint64_t* mask) {
+        if constexpr (PART == kEmitList) {
+            // lane 2 j + h writes half h of row j
+            uint64_t m = 0;
+            uint32_t first = 0, before = r;
+#pragma unroll
+            for (int j = 0; j < kRows; ++j) {
+                const bool mine = (lane >> 1) == j;
+                m = mine ? mask[j] : m;
+                first = mine ? before : first;
+                before += __popcll(mask[j]);
+            }
+            const uint32_t lo = uint32_t(m), hi = uint32_t(m >> 32);
+            if (lane < 2 * kRows)
+                table[1 + int64_t(u) * (kUnit / 32) + lane] =
+                    (lane & 1) ? RankWord{hi, first + uint32_t(__popc(lo))} : RankWord{lo, first};
+            ++u;
+        }
 #pragma unroll
         for (int j = 0; j < kRows; ++j) {
             // fluid lanes below this one in the row
             const uint32_t below = __builtin_amdgcn_mbcnt_hi(
                 uint32_t(mask[j] >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mask[j]), 0u));
             const bool fluid = (mask[j] >> lane) & 1u;
-            if (fluid) cell_of[r + below] = lin[j];
-            if (lin[j] >= 0) index_of[lin[j]] = fluid ? int32_t(r + below) : -1;
+            if (PART != kEmitIndex && fluid) cell_of[r + below] = lin[j];
+            if (PART != kEmitList && lin[j] >= 0) index_of[lin[j]] = fluid ? int32_t(r + below) : -1;
             r += __popcll(mask[j]);
         }
     });
@@ -566,32 +611,75 @@ __device__ __forceinline__ Steps steps_along(uint32_t x, uint32_t n, uint32_t pi
     return s;
 }
 
-// Rank of box cell `at` and of its two neighbours along x.
+// Ranks (-1: solid) of box cells at - 1, at and at + 1.
 struct Triple {
     int32_t v[3];
 };
 
-// One thread per fluid cell.  Its 18 index_of gathers are all in flight at
-// once (a neighbour outside a non-periodic face reads the cell's own entry and
-// is then discarded).  What bounds them is the address unit, which takes a
-// gather's cache lines one by one: 64 consecutive fluid cells of a packing lie
-// on about six lines of a box row.  The 14 neighbours on the five rows (y, z),
-// (y +- 1, z), (y, z +- 1) are therefore read as three consecutive words per
-// row, 9 gathers for 18; only cells on the box's x faces read them one by one.
-// The rows written (72 of the 80 bytes a cell moves) go past the caches, which
-// are left to index_of.  6.9 M cells of a 256^3 packing: 97 us, 5.7 TB/s (153
-// with cached stores); 4.8 M cells of a Hilbert-ordered channel 69 us (121 with
-// 18 gathers and cached stores); 30.6 M cells of a 384 x 384 x 512 packing,
-// whose index_of does not fit the last-level cache, 690 us (750): there the
-// gathers wait about 2,100 cycles for memory that the stores keep busy.  Runs
-// of 32 blocks per XCD: 10 % faster than one eighth each, 3 % than no runs.
-__global__ __launch_bounds__(256) void k_adjacency(const int32_t* __restrict__ cell_of,
-                                                   const int32_t* __restrict__ index_of, int64_t nf,
-                                                   AdjGeom g, XcdMap map,
+__device__ __forceinline__ int32_t rank_in(RankWord w, uint32_t bit) {
+    return (w.mask >> bit) & 1u ? int32_t(w.rank + __popc(w.mask & ((1u << bit) - 1))) : -1;
+}
+
+// Where the ranks come from: index_of, or the rank words of a lexicographic
+// list (the words of at - 1 and the one after it in one access).
+struct FromIndex {
+    const int32_t* __restrict__ index_of;
+    __device__ __forceinline__ int32_t one(uint32_t at) const { return index_of[at]; }
+    __device__ __forceinline__ Triple three(uint32_t at) const {
+        return *reinterpret_cast<const Triple*>(index_of + at - 1);
+    }
+};
+
+struct FromTable {
+    const RankWord* __restrict__ table;
+    __device__ __forceinline__ int32_t one(uint32_t at) const {
+        return rank_in(table[(at >> 5) + 1], at & 31u);
+    }
+    __device__ __forceinline__ Triple three(uint32_t at) const {
+        struct Two {
+            RankWord w[2];
+        };
+        const uint32_t first = at + 31u;  // cell at - 1, counted from the table's first word
+        const Two two = *reinterpret_cast<const Two*>(table + (first >> 5));
+        const uint32_t bit = first & 31u;
+        const uint64_t mask = two.w[0].mask | uint64_t(two.w[1].mask) << 32;
+        const uint32_t bits = uint32_t(mask >> bit);  // of the three cells, from the lowest
+        // the second word's rank is the first's plus its fluid cells
+        uint32_t r = two.w[0].rank + __popc(two.w[0].mask & ((1u << bit) - 1));
+        Triple t;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            t.v[j] = (bits >> j) & 1u ? int32_t(r) : -1;
+            r += (bits >> j) & 1u;
+        }
+        return t;
+    }
+};
+
+// One thread per fluid cell.  Its rank lookups are all in flight at once (a
+// neighbour outside a non-periodic face reads the cell's own entry and is then
+// discarded).  What bounds them is the address unit, which takes a gather's
+// cache lines one by one: 64 consecutive fluid cells of a packing lie on about
+// six lines of a box row of index_of.  The 14 neighbours on the five rows (y,
+// z), (y +- 1, z), (y, z +- 1) are therefore read three along x at a time, 9
+// gathers for 18; only cells on the box's x faces read them one by one.  The
+// rows written (72 of the 80 bytes a cell moves) go past the caches, which are
+// left to the ranks.  6.9 M cells of a 256^3 packing: 97 us, 5.7 TB/s (153 with
+// cached stores); 4.8 M cells of a Hilbert-ordered channel 69 us (121 with 18
+// gathers and cached stores).  30.6 M cells of a 384 x 384 x 512 packing, whose
+// index_of does not fit the last-level cache: the gathers wait about 2,100
+// cycles for memory that the stores keep busy, 690 us, of which the stores by
+// themselves take 437; a large lexicographic list reads rank words instead (381
+// us).  Runs of consecutive blocks per XCD: 8 or 32, 3 to 6 % faster than one
+// eighth each.
+// STREAM: cell_of comes in through nontemporal loads; see the launch.
+template <bool STREAM, class Ranks>
+__global__ __launch_bounds__(256) void k_adjacency(const int32_t* __restrict__ cell_of, Ranks ranks,
+                                                   int64_t nf, AdjGeom g, XcdMap map,
                                                    uint32_t* __restrict__ adj) {
     const int64_t m = logical_block(map) * 256 + threadIdx.x;
     if (m >= nf) return;
-    const uint32_t lin = uint32_t(cell_of[m]);
+    const uint32_t lin = uint32_t(STREAM ? __builtin_nontemporal_load(cell_of + m) : cell_of[m]);
     uint32_t x = lin;
     uint32_t y = div_rem(x, g.nx);
     const uint32_t z = div_rem(y, g.ny);
@@ -607,9 +695,9 @@ __global__ __launch_bounds__(256) void k_adjacency(const int32_t* __restrict__ c
             for (int cz = 0; cz < 3; ++cz) {
                 const uint32_t at = sy.out[cy] || sz.out[cz] ? lin : lin + sy.add[cy] + sz.add[cz];
                 if (cy == 1 || cz == 1)
-                    row[cy][cz] = *reinterpret_cast<const Triple*>(index_of + at - 1);
+                    row[cy][cz] = ranks.three(at);
                 else
-                    row[cy][cz].v[1] = index_of[at];
+                    row[cy][cz].v[1] = ranks.one(at);
             }
 #pragma unroll
         for (int k = 0; k < Q - 1; ++k)
@@ -619,7 +707,7 @@ __global__ __launch_bounds__(256) void k_adjacency(const int32_t* __restrict__ c
         for (int k = 0; k < Q - 1; ++k) {
             const int cx = vel_x(k + 1) + 1, cy = vel_y(k + 1) + 1, cz = vel_z(k + 1) + 1;
             const bool out = sx.out[cx] || sy.out[cy] || sz.out[cz];
-            up[k] = index_of[out ? lin : lin + sx.add[cx] + sy.add[cy] + sz.add[cz]];
+            up[k] = ranks.one(out ? lin : lin + sx.add[cx] + sy.add[cy] + sz.add[cz]);
         }
     }
     const uint32_t self = g.base + uint32_t(m);
@@ -789,18 +877,43 @@ extern "C" lbm_status lbm_build_adjacency(const lbm_geom* g, const uint8_t* flag
     if (nf > cap) return LBM_ECAPACITY;
     if (adj && stride < base + nf) return LBM_EINVAL;
 
-    with_order(ks.order, [&](auto order) {
-        k_emit<order><<<walk_grid, dim3(kWalkBlock), 0, s>>>(
-            ks, flag, uint32_t(units), uint32_t(per), uint32_t(groups), group_count, idx, cell_of);
-    });
-    if (hipGetLastError() != hipSuccess) return LBM_EHIP;
+    // A large lexicographic list with adjacency: the rank words lie in idx until
+    // the adjacency has been found, and the index is written over them.
+    RankWord* table = ks.order == LBM_ORDER_LEX && adj && nf > 0 && n_box >= kTableBox &&
+                              reinterpret_cast<uintptr_t>(idx) % sizeof(RankWord) == 0
+                          ? reinterpret_cast<RankWord*>(idx) : nullptr;
+    const auto emit = [&](auto order, auto part) {
+        k_emit<order, part><<<walk_grid, dim3(kWalkBlock), 0, s>>>(
+            ks, flag, uint32_t(units), uint32_t(per), uint32_t(groups), group_count, idx, cell_of, table);
+        return after_launch();
+    };
+    constexpr auto lex = std::integral_constant<int, LBM_ORDER_LEX>{};
+    lbm_status st = LBM_OK;
+    if (table)
+        st = emit(lex, std::integral_constant<int, kEmitList>{});
+    else
+        with_order(ks.order, [&](auto order) { st = emit(order, std::integral_constant<int, kEmitAll>{}); });
+    if (st != LBM_OK) return st;
     if (adj && nf > 0) {
         const AdjGeom ag{make_div(uint64_t(g->nx)), make_div(uint64_t(g->ny)), uint32_t(g->nz),
                          g->periodic, uint32_t(base), uint32_t(stride)};
         const int64_t blocks = (nf + 255) / 256;
-        const XcdMap map = map_of_runs(5);
-        k_adjacency<<<dim3(unsigned(virtual_blocks(blocks, map))), dim3(256), 0, s>>>(cell_of, idx, nf, ag, map, adj);
+        const XcdMap map = map_of_runs(table ? 3 : 5);
+        const dim3 grid{unsigned(virtual_blocks(blocks, map))};
+        // Flags, list and rank words that fit the last-level cache are still
+        // there; if they do not, the list is kept from displacing the words
+        // (54 M cells of a 512^3 box, whole call 1,406 -> 1,221 us, 45.5 M of
+        // 384 x 384 x 512 907 -> 807; 30.6 M cells of that box 573, 595 if
+        // streamed).
+        const bool stream = n_box + n_box / 4 + 4 * nf > int64_t(kCachedBytes);
+        if (!table)
+            k_adjacency<false><<<grid, dim3(256), 0, s>>>(cell_of, FromIndex{idx}, nf, ag, map, adj);
+        else if (stream)
+            k_adjacency<true><<<grid, dim3(256), 0, s>>>(cell_of, FromTable{table}, nf, ag, map, adj);
+        else
+            k_adjacency<false><<<grid, dim3(256), 0, s>>>(cell_of, FromTable{table}, nf, ag, map, adj);
         if (hipGetLastError() != hipSuccess) return LBM_EHIP;
     }
+    if (table) return emit(lex, std::integral_constant<int, kEmitIndex>{});
     return LBM_OK;
 }
