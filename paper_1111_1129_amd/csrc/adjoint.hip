@@ -23,12 +23,18 @@ namespace lbm {
 
 constexpr int kAdjBlock = 256;
 // Bytes per cell (sweep_launch): lambda^{t+1}, lambda^t, and f_t twice, since
-// every step of the reverse sweep reads another state.  Without the flag the
-// stores are nontemporal up to 1.25 GiB of that: 8-bit codes, 1.1 / 2.0 M
-// cells, 94 / 193 us a step against 108 / 200 with plain stores, but 4.0 /
-// 7.8 M cells 411 / 793 against 393 / 775.
+// every step of the reverse sweep reads another state.
 constexpr size_t kAdjCellBytes = 4 * Q * sizeof(double);
-constexpr size_t kAdjMaxNt = size_t(5) << 28;
+// Up to here the kernels are built for three waves per SIMD; beyond it steps
+// with plain stores alternate their direction (8-bit codes, 2.9 / 4.0 / 7.8 M
+// cells 288 / 396 / 780 -> 278 / 387 / 771 us; 2.0 M cells 193 -> 195).
+constexpr size_t kAdjThreeWaves = size_t(5) << 28;
+
+inline SweepLaunch adjoint_launch(int32_t flags, int64_t n) {
+    SweepLaunch l = sweep_launch(flags, n, kAdjCellBytes, false, false);
+    l.alternate = l.alternate && size_t(n) * kAdjCellBytes > kAdjThreeWaves;
+    return l;
+}
 
 // Waves per SIMD that the kernels are built for.  A cell holds 38 gathered and
 // read values in FP64, and the compiler takes 188 registers (two waves) unless
@@ -39,7 +45,7 @@ constexpr size_t kAdjMaxNt = size_t(5) << 28;
 template <class F>
 lbm_status with_policy_waves(int policy, int64_t n, F&& f) {
     return with_policy(policy, [&](auto pol) {
-        return size_t(n) * kAdjCellBytes <= kAdjMaxNt ? f(pol, std::integral_constant<int, 3>{})
+        return size_t(n) * kAdjCellBytes <= kAdjThreeWaves ? f(pol, std::integral_constant<int, 3>{})
                                                       : f(pol, std::integral_constant<int, 2>{});
     });
 }
@@ -216,10 +222,11 @@ extern "C" lbm_status lbm_step_adjoint(const lbm_params* p, int64_t n, int64_t s
     const TrtConst c = make_trt_const(*p);
     const double* f = static_cast<const double*>(f_t);
     // the sweep's launch options: workgroup-to-XCD mapping, memory policy
-    const SweepLaunch l = sweep_launch(p->flags, n, kAdjCellBytes, kAdjMaxNt);
+    const SweepLaunch l = adjoint_launch(p->flags, n);
+    const XcdMap map = l.towards(lam_t < lam_next);
     return with_policy_waves(l.policy, n, [&](auto pol, auto waves) {
-        if (ns) k_adjoint<true, pol, waves><<<l.grid, l.block, 0, s>>>(f, adj, ns, lam_next, lam_t, grad_ns, n, stride, c, l.map);
-        else k_adjoint<false, pol, waves><<<l.grid, l.block, 0, s>>>(f, adj, ns, lam_next, lam_t, nullptr, n, stride, c, l.map);
+        if (ns) k_adjoint<true, pol, waves><<<l.grid, l.block, 0, s>>>(f, adj, ns, lam_next, lam_t, grad_ns, n, stride, c, map);
+        else k_adjoint<false, pol, waves><<<l.grid, l.block, 0, s>>>(f, adj, ns, lam_next, lam_t, nullptr, n, stride, c, map);
         return after_launch();
     });
 }
@@ -240,10 +247,11 @@ lbm_status step_adjoint_coded(const lbm_params* p, int64_t n, int64_t stride,
     hipStream_t s = as_stream(stream);
     const TrtConst c = make_trt_const(*p);
     const double* f = static_cast<const double*>(f_t);
-    const SweepLaunch l = sweep_launch(p->flags, n, kAdjCellBytes, kAdjMaxNt);
+    const SweepLaunch l = adjoint_launch(p->flags, n);
+    const XcdMap map = l.towards(lam_t < lam_next);
     return with_policy_waves(l.policy, n, [&](auto pol, auto waves) {
-        if (ns) k_adjoint_coded<true, pol, C8, waves><<<l.grid, l.block, 0, s>>>(f, codes8, codes, tile_records, adj, ns, lam_next, lam_t, grad_ns, n, stride, c, l.map);
-        else k_adjoint_coded<false, pol, C8, waves><<<l.grid, l.block, 0, s>>>(f, codes8, codes, tile_records, adj, ns, lam_next, lam_t, nullptr, n, stride, c, l.map);
+        if (ns) k_adjoint_coded<true, pol, C8, waves><<<l.grid, l.block, 0, s>>>(f, codes8, codes, tile_records, adj, ns, lam_next, lam_t, grad_ns, n, stride, c, map);
+        else k_adjoint_coded<false, pol, C8, waves><<<l.grid, l.block, 0, s>>>(f, codes8, codes, tile_records, adj, ns, lam_next, lam_t, nullptr, n, stride, c, map);
         return after_launch();
     });
 }

@@ -303,12 +303,6 @@ struct BatchLaunch {
     void* barrier;  // persistent only
 };
 
-// Bytes a step touches per cell (sweep_launch).
-template <int ST>
-size_t cell_bytes(int src) {
-    return 2 * Q * sizeof(typename Storage<ST>::T) + (Q - 1) * (src == kC8 ? 1 : src == kC16 ? 2 : 4);
-}
-
 template <int ST, bool PBB, int POL, int SRC>
 lbm_status launch_table_steps(const BatchLaunch& L, const SweepLaunch& l, hipStream_t s) {
     using T = typename Storage<ST>::T;
@@ -319,7 +313,7 @@ lbm_status launch_table_steps(const BatchLaunch& L, const SweepLaunch& l, hipStr
         T* dst = (k & 1) ? a : b;
         k_trt_table<ST, PBB, POL, SRC><<<l.grid, l.block, 0, s>>>(src, dst, L.codes8, L.codes, L.rec, L.adj,
                                                         L.ns, L.n, L.stride, L.tab.entries,
-                                                        L.tab.tile_param, l.map);
+                                                        L.tab.tile_param, l.towards(dst < src));
         if (hipGetLastError() != hipSuccess) return LBM_EHIP;
     }
     return LBM_OK;
@@ -375,8 +369,8 @@ lbm_status launch_persistent_t(const BatchLaunch& L, const SweepLaunch& l, hipSt
 // A persistent workgroup takes groups of kGroupTiles tiles, a per-step one a tile.
 template <int ST, bool PBB, int SRC>
 lbm_status launch_batch_src(const BatchLaunch& L, bool persistent, hipStream_t s) {
-    const SweepLaunch l = sweep_launch(L.flags, L.n, cell_bytes<ST>(SRC), sweep_max_nt(ST),
-                                       persistent ? kPThreads : kBBlock);
+    const SweepLaunch l = two_array_launch<ST>(L.flags, L.n, SRC == kC8 ? 1 : SRC == kC16 ? 2 : 4,
+                                               persistent ? kPThreads : kBBlock);
     return with_policy(l.policy, [&](auto pol) {
         return persistent ? launch_persistent_t<ST, PBB, pol, SRC>(L, l, s)
                           : launch_table_steps<ST, PBB, pol, SRC>(L, l, s);

@@ -296,16 +296,16 @@ lbm_status launch_coded(const lbm_params& p, int64_t n, int64_t stride, const in
     T* a = static_cast<T*>(fa);
     T* b = static_cast<T*>(fb);
     const TrtConst c = make_trt_const(p);
-    const SweepLaunch l = sweep_launch(p.flags, n, 2 * Q * sizeof(T) + (Q - 1) * (codes8 ? 1 : 2),
-                                       sweep_max_nt(ST));
+    const SweepLaunch l = two_array_launch<ST>(p.flags, n, codes8 ? 1 : 2);
     return with_policy(l.policy, [&](auto pol) -> lbm_status {
         for (int k = 0; k < n_steps; ++k) {
             const T* src = (k & 1) ? b : a;
             T* dst = (k & 1) ? a : b;
+            const XcdMap map = l.towards(dst < src);
             if (codes8)
-                k_trt_c8<ST, PBB, pol><<<l.grid, l.block, 0, s>>>(src, dst, codes8, codes, toff, adj, ns, n, stride, c, l.map);
+                k_trt_c8<ST, PBB, pol><<<l.grid, l.block, 0, s>>>(src, dst, codes8, codes, toff, adj, ns, n, stride, c, map);
             else
-                k_trt_c16<ST, PBB, pol><<<l.grid, l.block, 0, s>>>(src, dst, codes, toff, adj, ns, n, stride, c, l.map);
+                k_trt_c16<ST, PBB, pol><<<l.grid, l.block, 0, s>>>(src, dst, codes, toff, adj, ns, n, stride, c, map);
             if (hipGetLastError() != hipSuccess) return LBM_EHIP;
         }
         return LBM_OK;

@@ -156,23 +156,26 @@ lbm_status launch_inplace(const lbm_params& p, int64_t n, int64_t stride, const 
     using T = typename Storage<ST>::T;
     T* f = static_cast<T*>(fv);
     const TrtConst c = make_trt_const(p);
-    // nontemporal stores without the flag in every storage: the local step
-    // writes whole lines that it has just read (shifted FP32 12.7 / 30.6 M
+    // nontemporal stores without the flag in FP64 and over 8-bit codes: the local
+    // step writes whole lines that it has just read (shifted FP32 12.7 / 30.6 M
     // cells 405 / 999 us a sweep against 427 / 1,025 with plain stores, scaled
-    // FP16 232 / 598 against 248 / 616), the gather-scatter step does not mind
+    // FP16 232 / 598 against 248 / 616), the gather-scatter step does not mind.
+    // With them both steps run forwards (backwards local steps cost 1 to 5 %).
     const SweepLaunch l = sweep_launch(p.flags, n, Q * sizeof(T) + (Q - 1) * (codes8 ? 1 : codes ? 2 : 4),
-                                       SIZE_MAX);
+                                       sizeof(T) == 8 || codes8, false);
     return with_policy(l.policy, [&](auto pol) -> lbm_status {
         for (int k = 0; k < n_steps; ++k) {
-            if (((phase + k) & 1) == 0) {
+            const bool local = (phase + k) & 1;
+            const XcdMap map = l.towards(local);
+            if (!local) {
                 if (codes8)
-                    k_gather_scatter<ST, PBB, pol, kFrom8><<<l.grid, l.block, 0, s>>>(f, adj, codes, codes8, rec, ns, n, stride, c, l.map);
+                    k_gather_scatter<ST, PBB, pol, kFrom8><<<l.grid, l.block, 0, s>>>(f, adj, codes, codes8, rec, ns, n, stride, c, map);
                 else if (codes)
-                    k_gather_scatter<ST, PBB, pol, kFrom16><<<l.grid, l.block, 0, s>>>(f, adj, codes, codes8, rec, ns, n, stride, c, l.map);
+                    k_gather_scatter<ST, PBB, pol, kFrom16><<<l.grid, l.block, 0, s>>>(f, adj, codes, codes8, rec, ns, n, stride, c, map);
                 else
-                    k_gather_scatter<ST, PBB, pol, kFromAdj><<<l.grid, l.block, 0, s>>>(f, adj, codes, codes8, rec, ns, n, stride, c, l.map);
+                    k_gather_scatter<ST, PBB, pol, kFromAdj><<<l.grid, l.block, 0, s>>>(f, adj, codes, codes8, rec, ns, n, stride, c, map);
             } else {
-                k_local<ST, PBB, pol><<<l.grid, l.block, 0, s>>>(f, ns, n, stride, c, l.map);
+                k_local<ST, PBB, pol><<<l.grid, l.block, 0, s>>>(f, ns, n, stride, c, map);
             }
             if (hipGetLastError() != hipSuccess) return LBM_EHIP;
         }

@@ -324,16 +324,21 @@ constexpr int NXCD = 8;
 // below 2^31: a list has fewer than 2^32 / 19 cells.
 struct XcdMap {
     uint32_t group_shift, run, mask;
+    uint32_t flip, off;  // ~0 and the block count: from the last block to the first
 };
 
-constexpr XcdMap map_of_runs(int shift) { return XcdMap{3u + shift, 1u << shift, (1u << shift) - 1}; }
+constexpr XcdMap map_of_runs(int shift) {
+    return XcdMap{3u + shift, 1u << shift, (1u << shift) - 1, 0u, 0u};
+}
 constexpr XcdMap map_of_eighths(int64_t blocks) {
-    return XcdMap{31u, uint32_t((blocks + NXCD - 1) / NXCD), ~0u};
+    return XcdMap{31u, uint32_t((blocks + NXCD - 1) / NXCD), ~0u, 0u, 0u};
 }
 
+// (Padding blocks of a flipped map wrap to indices above every block.)
 __device__ __forceinline__ uint32_t logical_of(uint32_t v, XcdMap map) {
-    return ((v >> map.group_shift) << map.group_shift) + (v & (NXCD - 1)) * map.run +
-           ((v >> 3) & map.mask);
+    const uint32_t b = ((v >> map.group_shift) << map.group_shift) + (v & (NXCD - 1)) * map.run +
+                       ((v >> 3) & map.mask);
+    return (b ^ map.flip) + map.off;
 }
 
 __device__ __forceinline__ int64_t logical_block(XcdMap map) { return logical_of(blockIdx.x, map); }
@@ -342,11 +347,6 @@ __device__ __forceinline__ int64_t logical_block(XcdMap map) { return logical_of
 __host__ __device__ inline int64_t virtual_blocks(int64_t blocks, XcdMap map) {
     const int64_t q = int64_t(NXCD) * map.run;
     return (blocks + q - 1) / q * q;
-}
-
-// max_nt_bytes of the sweeps of a storage form.
-constexpr size_t sweep_max_nt(int storage) {
-    return storage == LBM_F64 || storage == LBM_F64_SHIFTED ? SIZE_MAX : 0;
 }
 
 // Launch of a sweep over n cells, one workgroup per 256-cell tile: the memory
@@ -368,12 +368,17 @@ constexpr size_t sweep_max_nt(int storage) {
 //    loaded (FP64 full list, 7.5 M cells: 525 us against 554 with an eighth
 //    each; shifted FP32 over codes, 3.6 M: 123 against 137).  Runs of 4 to 64
 //    tiles are within 1 % of it.
-//  * nontemporal stores with LBM_FLAG_NONTEMPORAL, and in FP64 beyond 384 MiB
-//    also without it: there they were faster at every size, ordering and form
-//    (full list 3.3 / 12.7 / 23 / 54 M cells: 223 / 878 / 1,529 / 3,639 us
-//    against 234 / 882 / 1,586 / 3,790; blocked order 8 M box cells 240
-//    against 254), while the narrower storages go either way (shifted FP32
-//    full list: 23 M cells 876 against 926, 12.7 M cells 546 against 530).
+//  * nontemporal stores with LBM_FLAG_NONTEMPORAL, and beyond 384 MiB also
+//    without it where they are faster nearly always: in FP64 (14 random boxes,
+//    3 orderings, full list and 16-bit codes: -7 to +0.5 %, median -3.5 %) and
+//    over 8-bit codes (narrower storages: -13 to 0 %, median -5 %).  Narrower
+//    storages over the other forms go either way (-9 to +7 %).
+//  * beyond 384 MiB with plain stores, or over 8-bit codes, every other sweep
+//    runs from the last tile to the first: it begins with what the one before
+//    left in the last-level cache.  Same boxes: plain -11 to +0.4 %, median
+//    -3.5 %; nontemporal over 8-bit codes -4 to +1 %, median -1 % (shifted FP32
+//    612 MB 113.4 -> 108.7 us, FP64 402 MB 77.4 -> 74.0); nontemporal over the
+//    other forms -1 to +2 %, so those keep one direction.
 constexpr size_t kCachedBytes = size_t(240) << 20;
 constexpr size_t kContiguousBytes = size_t(384) << 20;
 
@@ -381,18 +386,31 @@ struct SweepLaunch {
     dim3 grid, block;
     XcdMap map;
     int policy;
+    bool alternate;  // sweeps towards the lower of two arrays run backwards
+    uint32_t blocks;
+
+    XcdMap towards(bool lower) const {
+        XcdMap m = map;
+        if (alternate && lower) {
+            m.flip = ~0u;
+            m.off = blocks;
+        }
+        return m;
+    }
 };
 
-// max_nt_bytes: largest state that takes nontemporal stores without the flag;
-// block: list cells per workgroup (a multiple of the 256-cell tile).
-inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, size_t max_nt_bytes,
-                                int block = kCodeTile) {
+// nt: nontemporal stores beyond 384 MiB also without the flag; alternate_nt:
+// directions alternate with nontemporal stores too; block: list cells per
+// workgroup (a multiple of the 256-cell tile).
+inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, bool nt,
+                                bool alternate_nt, int block = kCodeTile) {
     const size_t bytes = size_t(n) * cell_bytes;
     const int64_t blocks = std::max<int64_t>(1, (n + block - 1) / block);
     const int64_t given = (flags & LBM_FLAG_XCD_CHUNK_MASK) >> LBM_FLAG_XCD_CHUNK_SHIFT;
-    const bool cached = bytes <= kCachedBytes;
+    const bool cached = bytes <= kCachedBytes, large = bytes > kContiguousBytes;
     SweepLaunch l;
-    if (cached || (given == 0 && bytes <= kContiguousBytes)) {
+    l.blocks = uint32_t(blocks);
+    if (cached || (given == 0 && !large)) {
         l.map = map_of_eighths(blocks);
     } else {
         const int64_t run = (given ? given : 8) * kCodeTile / block;
@@ -400,12 +418,20 @@ inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, siz
         while ((int64_t(2) << shift) <= run) ++shift;
         l.map = map_of_runs(shift);
     }
-    const bool nt = (flags & LBM_FLAG_NONTEMPORAL) ||
-                    (bytes > kContiguousBytes && bytes <= max_nt_bytes);
-    l.policy = cached ? kCached : nt ? kStreamNT : kStream;
+    l.policy = cached ? kCached : (flags & LBM_FLAG_NONTEMPORAL) || (large && nt) ? kStreamNT : kStream;
+    l.alternate = large && (l.policy == kStream || alternate_nt);
     l.grid = dim3(unsigned(virtual_blocks(blocks, l.map)));
     l.block = dim3(unsigned(block));
     return l;
+}
+
+// The two-array sweep of a storage form over the full list or 16- or 8-bit
+// codes (code_bytes 4, 2, 1).
+template <int ST>
+inline SweepLaunch two_array_launch(int32_t flags, int64_t n, size_t code_bytes, int block = kCodeTile) {
+    constexpr size_t T = sizeof(typename Storage<ST>::T);
+    return sweep_launch(flags, n, 2 * Q * T + (Q - 1) * code_bytes, T == 8 || code_bytes == 1,
+                        code_bytes == 1, block);
 }
 
 // Calls f(std::integral_constant<int, policy>).

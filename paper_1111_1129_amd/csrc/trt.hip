@@ -94,13 +94,13 @@ lbm_status launch_steps(const lbm_params& p, int64_t n, int64_t stride, const ui
     T* a = static_cast<T*>(fa);
     T* b = static_cast<T*>(fb);
     const TrtConst c = make_trt_const(p);
-    const SweepLaunch l = sweep_launch(p.flags, n, 2 * Q * sizeof(T) + (Q - 1) * sizeof(uint32_t),
-                                       sweep_max_nt(ST));
+    const SweepLaunch l = two_array_launch<ST>(p.flags, n, sizeof(uint32_t));
     return with_policy(l.policy, [&](auto pol) -> lbm_status {
         for (int k = 0; k < n_steps; ++k) {
             const T* src = (k & 1) ? b : a;
             T* dst = (k & 1) ? a : b;
-            k_trt<ST, PBB, pol><<<l.grid, l.block, 0, s>>>(src, dst, adj, ns, n, stride, c, l.map);
+            k_trt<ST, PBB, pol><<<l.grid, l.block, 0, s>>>(src, dst, adj, ns, n, stride, c,
+                                                                  l.towards(dst < src));
             if (hipGetLastError() != hipSuccess) return LBM_EHIP;
         }
         return LBM_OK;

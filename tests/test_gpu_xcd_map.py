@@ -1,7 +1,8 @@
 """The library's own workgroup-to-XCD mapping (xcd_chunk = 0) at the sizes where
 its runs end: fewer tiles than XCDs, whole and partial groups of runs, and both
-sides of the state size at which it goes over from one run per XCD to short
-runs.  Every form is bitwise the hardware order (xcd_chunk = 1)."""
+sides of the state sizes at which it goes over from one run per XCD to short
+runs and lets every other sweep run backwards.  Every form is bitwise the
+hardware order (xcd_chunk = 1)."""
 import pytest
 import torch
 
@@ -13,7 +14,7 @@ from gpu_helpers import dev_flags, print_case
 pytestmark = pytest.mark.gpu
 
 # cells of an all-fluid box: 1, 256, 257 (2 tiles), 7-9 tiles, 64 and 65 tiles,
-# and beyond 384 MB of state (2.6 M cells of 148 bytes)
+# and about 240 and 384 MiB of state (2.7 and 3.3 M cells of 76 to 148 bytes)
 BOXES = [(1, 1, 1), (16, 16, 1), (257, 1, 1), (16, 16, 7), (16, 16, 8), (16, 18, 8), (32, 32, 16),
          (33, 31, 17), (140, 139, 138), (150, 149, 147)]
 
@@ -34,15 +35,16 @@ def test_default_map_covers_every_cell_once(dims, storage):
     def states(chunk):
         prm = L.params(0.8, 3 / 16, (1e-5, 0, 0), storage, xcd_chunk=chunk)
         out = []
-        for form in ("full", "c16", "c8", "inplace", "persistent"):
-            st = L.init_inplace(lat, prm) if form == "inplace" else L.init(lat, prm)
+        for form in ("full", "c16", "c8", "inplace", "persistent", "inplace_full"):
+            st = (L.init_inplace if form.startswith("inplace") else L.init)(lat, prm)
             st.f[:, :n] = f0
             if form == "full":
                 L.step(st, 2)
             elif form == "c16":
                 L.step_c16(st, comp, 2)
-            elif form == "inplace":
-                L.step_inplace(st, 2, comp, c8=True)
+            elif form.startswith("inplace"):
+                full = form.endswith("full")
+                L.step_inplace(st, 2, None if full else comp, c8=not full)
             else:
                 L.step_c8(st, comp, 2, persistent=form == "persistent")
             out.append(st.f[:, :n])
@@ -57,7 +59,7 @@ def test_default_map_covers_every_cell_once(dims, storage):
         return out
 
     ref = states(1)
-    for a in ref[1:5]:
+    for a in ref[1:6]:
         assert torch.equal(a, ref[0])
     for a, b in zip(states(0), ref):
         assert torch.equal(a, b)
