@@ -107,7 +107,6 @@ __device__ __forceinline__ TrtConst tile_const(const ParamEntry* __restrict__ en
     TrtConst c;
     c.sp = e.sp;
     c.sm = e.sm;
-    c.G[0] = c.G[1] = c.G[2] = 0.0;  // the sweep uses the force through F only
 #pragma unroll
     for (int q = 0; q < NPAIR; ++q) c.F[q] = e.F[q];
     return c;
@@ -308,13 +307,14 @@ lbm_status launch_table_steps(const BatchLaunch& L, const SweepLaunch& l, hipStr
     using T = typename Storage<ST>::T;
     T* a = static_cast<T*>(L.fa);
     T* b = static_cast<T*>(L.fb);
+    const BoundKernel kernel(k_trt_table<ST, PBB, POL, SRC>, l.grid, l.block, s);
     for (int k = 0; k < L.n_steps; ++k) {
         const T* src = (k & 1) ? b : a;
         T* dst = (k & 1) ? a : b;
-        k_trt_table<ST, PBB, POL, SRC><<<l.grid, l.block, 0, s>>>(src, dst, L.codes8, L.codes, L.rec, L.adj,
-                                                        L.ns, L.n, L.stride, L.tab.entries,
-                                                        L.tab.tile_param, l.towards(dst < src));
-        if (hipGetLastError() != hipSuccess) return LBM_EHIP;
+        if (lbm_status st = kernel(src, dst, L.codes8, L.codes, L.rec, L.adj, L.ns, L.n, L.stride,
+                                   L.tab.entries, L.tab.tile_param, l.towards(dst < src));
+            st != LBM_OK)
+            return st;
     }
     return LBM_OK;
 }

@@ -298,17 +298,24 @@ lbm_status launch_coded(const lbm_params& p, int64_t n, int64_t stride, const in
     const TrtConst c = make_trt_const(p);
     const SweepLaunch l = two_array_launch<ST>(p.flags, n, codes8 ? 1 : 2);
     return with_policy(l.policy, [&](auto pol) -> lbm_status {
-        for (int k = 0; k < n_steps; ++k) {
-            const T* src = (k & 1) ? b : a;
-            T* dst = (k & 1) ? a : b;
-            const XcdMap map = l.towards(dst < src);
-            if (codes8)
-                k_trt_c8<ST, PBB, pol><<<l.grid, l.block, 0, s>>>(src, dst, codes8, codes, toff, adj, ns, n, stride, c, map);
-            else
-                k_trt_c16<ST, PBB, pol><<<l.grid, l.block, 0, s>>>(src, dst, codes, toff, adj, ns, n, stride, c, map);
-            if (hipGetLastError() != hipSuccess) return LBM_EHIP;
+        const auto steps = [&](auto&& sweep) -> lbm_status {
+            for (int k = 0; k < n_steps; ++k) {
+                const T* src = (k & 1) ? b : a;
+                T* dst = (k & 1) ? a : b;
+                if (lbm_status st = sweep(src, dst, l.towards(dst < src)); st != LBM_OK) return st;
+            }
+            return LBM_OK;
+        };
+        if (codes8) {
+            const BoundKernel kernel(k_trt_c8<ST, PBB, pol>, l.grid, l.block, s);
+            return steps([&](const T* src, T* dst, XcdMap map) {
+                return kernel(src, dst, codes8, codes, toff, adj, ns, n, stride, c, map);
+            });
         }
-        return LBM_OK;
+        const BoundKernel kernel(k_trt_c16<ST, PBB, pol>, l.grid, l.block, s);
+        return steps([&](const T* src, T* dst, XcdMap map) {
+            return kernel(src, dst, codes, toff, adj, ns, n, stride, c, map);
+        });
     });
 }
 

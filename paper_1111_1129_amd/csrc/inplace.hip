@@ -164,20 +164,17 @@ lbm_status launch_inplace(const lbm_params& p, int64_t n, int64_t stride, const 
     const SweepLaunch l = sweep_launch(p.flags, n, Q * sizeof(T) + (Q - 1) * (codes8 ? 1 : codes ? 2 : 4),
                                        sizeof(T) == 8 || codes8, false);
     return with_policy(l.policy, [&](auto pol) -> lbm_status {
+        const BoundKernel local(k_local<ST, PBB, pol>, l.grid, l.block, s);
+        const BoundKernel scatter(codes8  ? k_gather_scatter<ST, PBB, pol, kFrom8>
+                                  : codes ? k_gather_scatter<ST, PBB, pol, kFrom16>
+                                          : k_gather_scatter<ST, PBB, pol, kFromAdj>,
+                                  l.grid, l.block, s);
         for (int k = 0; k < n_steps; ++k) {
-            const bool local = (phase + k) & 1;
-            const XcdMap map = l.towards(local);
-            if (!local) {
-                if (codes8)
-                    k_gather_scatter<ST, PBB, pol, kFrom8><<<l.grid, l.block, 0, s>>>(f, adj, codes, codes8, rec, ns, n, stride, c, map);
-                else if (codes)
-                    k_gather_scatter<ST, PBB, pol, kFrom16><<<l.grid, l.block, 0, s>>>(f, adj, codes, codes8, rec, ns, n, stride, c, map);
-                else
-                    k_gather_scatter<ST, PBB, pol, kFromAdj><<<l.grid, l.block, 0, s>>>(f, adj, codes, codes8, rec, ns, n, stride, c, map);
-            } else {
-                k_local<ST, PBB, pol><<<l.grid, l.block, 0, s>>>(f, ns, n, stride, c, map);
-            }
-            if (hipGetLastError() != hipSuccess) return LBM_EHIP;
+            const bool at_home = (phase + k) & 1;
+            const XcdMap map = l.towards(at_home);
+            const lbm_status st = at_home ? local(f, ns, n, stride, c, map)
+                                          : scatter(f, adj, codes, codes8, rec, ns, n, stride, c, map);
+            if (st != LBM_OK) return st;
         }
         return LBM_OK;
     });

@@ -144,7 +144,6 @@ constexpr int32_t kCode8Max = 127;
 // ---------------------------------------------------------------------------
 struct TrtConst {
     double sp, sm;       // s+ = 1/tau+, s- = 1/tau-
-    double G[3];         // body force
     double F[NPAIR];     // 3 w c.G for the odd member of each pair
 };
 
@@ -153,7 +152,6 @@ inline TrtConst make_trt_const(const lbm_params& p) {
     double tau_minus = 0.5 + p.magic / (p.tau_plus - 0.5);
     c.sp = 1.0 / p.tau_plus;
     c.sm = 1.0 / tau_minus;
-    for (int d = 0; d < 3; ++d) c.G[d] = p.force[d];
     for (int k = 0; k < NPAIR; ++k)
         c.F[k] = 3.0 * pair_weight(k) * (PCX[k] * p.force[0] + PCY[k] * p.force[1] + PCZ[k] * p.force[2]);
     return c;

@@ -25,6 +25,31 @@ inline lbm_status after_launch() {
 
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
+// A kernel that is launched many times in one call.  Its handle is looked up
+// once: the triple-chevron form finds it by its host address and passes the
+// launch shape through thread-local storage at every launch, which a sweep of
+// a few microseconds waits for.  The arguments are the kernel's own types.
+template <class... P>
+class BoundKernel {
+public:
+    BoundKernel(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t s)
+        : grid_(grid), block_(block), stream_(s),
+          found_(hipGetFuncBySymbol(&fn_, reinterpret_cast<const void*>(kernel)) == hipSuccess) {}
+
+    lbm_status operator()(P... args) const {
+        if (!found_) return LBM_EHIP;
+        void* ptrs[] = {static_cast<void*>(&args)...};
+        return hipModuleLaunchKernel(fn_, grid_.x, grid_.y, grid_.z, block_.x, block_.y, block_.z, 0,
+                                     stream_, ptrs, nullptr) == hipSuccess ? LBM_OK : LBM_EHIP;
+    }
+
+private:
+    hipFunction_t fn_ = nullptr;
+    dim3 grid_, block_;
+    hipStream_t stream_;
+    bool found_;
+};
+
 inline bool valid_storage(int st) { return st >= LBM_F64 && st <= LBM_F16_SHIFTED_SCALED; }
 
 // TRT parameters usable for a sweep: tau+ > 1/2 and tau- > 1/2 (magic > 0),
