@@ -49,8 +49,6 @@ namespace lbm {
 constexpr int kBBlock = kCodeTile;            // one workgroup = one tile of 256 cells
 constexpr long kSpinLimit = 1L << 27;         // polls of ~256 clocks: ~14 s, far above any step
 constexpr size_t kBarrierBytes = 256;         // workspace: barrier block
-constexpr int kParamsPerFill = 32;            // parameter sets per table-writing launch
-constexpr int kSegsPerFill = 256;             // segments per tile-index-writing launch
 
 // One parameter set as the sweep reads it (FP64, host-computed).
 struct ParamEntry {
@@ -60,19 +58,25 @@ struct ParamEntry {
 };
 static_assert(sizeof(ParamEntry) == 96, "ParamEntry layout");
 
-struct ParamChunk {
-    int count;
-    ParamEntry e[kParamsPerFill];
+// What a table-writing launch gets as arguments: parameter sets and segments
+// in the form that they are given in, up to kFill of each.
+constexpr int kFill = 64;
+
+struct FillParams {
+    double sp, sm, force[3];
 };
 
-struct SegTiles {
+struct FillSegs {
     int32_t first, last, param;  // tiles [first, last) use parameter set `param`
 };
 
-struct SegChunk {
-    int count;
-    SegTiles s[kSegsPerFill];
+struct FillChunk {
+    int32_t n_params, n_segs;
+    int64_t first_tile, last_tile;  // tiles that this launch writes
+    FillParams p[kFill];
+    FillSegs s[kFill];
 };
+static_assert(sizeof(FillChunk) < 3800, "fits the kernel arguments beside the pointers");
 
 // Table and per-tile index in the workspace.
 struct ParamTable {
@@ -80,20 +84,33 @@ struct ParamTable {
     const int32_t* tile_param;  // per tile, or nullptr: every tile uses entry 0
 };
 
-__global__ void k_write_params(ParamEntry* dst, ParamChunk chunk) {
-    const int i = threadIdx.x;
-    if (i < chunk.count) dst[i] = chunk.e[i];
-}
-
-__global__ void k_fill_i32(int32_t* p, int64_t count, int32_t v) {
+// Writes a chunk's parameter sets (force terms as make_trt_const forms them)
+// and the set of every tile in its range: 0 where no segment lies.
+__global__ void k_write_table(ParamEntry* __restrict__ dst, int32_t* __restrict__ tile_param,
+                              FillChunk chunk) {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = v;
-}
-
-// One workgroup per segment of the chunk: mark its tiles.
-__global__ void k_mark_tiles(int32_t* tile_param, SegChunk chunk) {
-    const SegTiles st = chunk.s[blockIdx.x];
-    for (int32_t t = st.first + int32_t(threadIdx.x); t < st.last; t += blockDim.x) tile_param[t] = st.param;
+    if (i < chunk.n_params) {
+        const FillParams& p = chunk.p[i];
+        ParamEntry e;
+        e.sp = p.sp;
+        e.sm = p.sm;
+#pragma unroll
+        for (int q = 0; q < NPAIR; ++q) e.F[q] = force_term(q, p.force);
+        e.pad = 0.0;
+        dst[i] = e;
+    }
+    const int64_t t = chunk.first_tile + i;
+    if (t < chunk.last_tile) {
+        int lo = 0, hi = chunk.n_segs;  // segments that begin at or before t
+        while (lo < hi) {
+            const int mid = (lo + hi) / 2;
+            if (chunk.s[mid].first <= t)
+                lo = mid + 1;
+            else
+                hi = mid;
+        }
+        tile_param[t] = lo > 0 && t < chunk.s[lo - 1].last ? chunk.s[lo - 1].param : 0;
+    }
 }
 
 // The TRT constants of a tile (uniform over the wave: scalar loads; the
@@ -422,40 +439,40 @@ lbm_status step_batch(const lbm_params* p, int32_t n_params, const lbm_segment* 
     char* ws = static_cast<char*>(workspace);
     auto* entries = reinterpret_cast<ParamEntry*>(ws + w.table_off);
     auto* tile_param = per_tile ? reinterpret_cast<int32_t*>(ws + w.tiles_off) : nullptr;
-    // parameter table, written from kernel arguments (nothing host-resident
-    // has to outlive the call)
-    for (int32_t k0 = 0; k0 < n_params; k0 += kParamsPerFill) {
-        ParamChunk ch;
-        ch.count = std::min<int32_t>(kParamsPerFill, n_params - k0);
-        for (int i = 0; i < ch.count; ++i) {
+    // table and tile index, written from kernel arguments (nothing
+    // host-resident has to outlive the call): one launch for up to kFill sets
+    // and segments.  The launch that begins with segment k writes the tiles
+    // from that segment's first (the first launch: from 0) to the next
+    // launch's.
+    const int64_t tiles = per_tile ? (n + kBBlock - 1) / kBBlock : 0;
+    int64_t written = 0;
+    for (int32_t k0 = 0, s0 = 0; k0 < n_params || written < tiles;) {
+        FillChunk ch;
+        ch.n_params = std::min<int32_t>(kFill, n_params - k0);
+        for (int i = 0; i < ch.n_params; ++i) {
             const TrtConst c = make_trt_const(p[k0 + i]);
-            ParamEntry& e = ch.e[i];
-            e.sp = c.sp;
-            e.sm = c.sm;
-            for (int q = 0; q < NPAIR; ++q) e.F[q] = c.F[q];
-            e.pad = 0.0;
+            ch.p[i].sp = c.sp;
+            ch.p[i].sm = c.sm;
+            for (int d = 0; d < 3; ++d) ch.p[i].force[d] = p[k0 + i].force[d];
         }
-        k_write_params<<<1, 64, 0, s>>>(entries + k0, ch);
-        if (hipGetLastError() != hipSuccess) return LBM_EHIP;
-    }
-    if (per_tile) {
-        const int64_t tiles = (n + kBBlock - 1) / kBBlock;
-        k_fill_i32<<<dim3(unsigned((tiles + 255) / 256)), 256, 0, s>>>(tile_param, tiles, 0);
-        if (hipGetLastError() != hipSuccess) return LBM_EHIP;
-        for (int32_t k0 = 0; k0 < n_seg; k0 += kSegsPerFill) {
-            SegChunk ch;
-            ch.count = 0;
-            for (int32_t k = k0; k < std::min<int32_t>(n_seg, k0 + kSegsPerFill); ++k) {
-                if (seg[k].n == 0) continue;
-                SegTiles& t = ch.s[ch.count++];
-                t.first = int32_t(seg[k].base / kBBlock);
-                t.last = int32_t((seg[k].base + seg[k].n + kBBlock - 1) / kBBlock);
-                t.param = seg[k].param_index;
+        ch.n_segs = 0;
+        ch.first_tile = written;
+        ch.last_tile = tiles;
+        for (; written < tiles && s0 < n_seg; ++s0) {
+            if (seg[s0].n == 0) continue;
+            const int32_t first = int32_t(seg[s0].base / kBBlock);
+            if (ch.n_segs == kFill) {
+                ch.last_tile = first;
+                break;
             }
-            if (ch.count == 0) continue;
-            k_mark_tiles<<<ch.count, 256, 0, s>>>(tile_param, ch);
-            if (hipGetLastError() != hipSuccess) return LBM_EHIP;
+            ch.s[ch.n_segs++] = FillSegs{first, int32_t((seg[s0].base + seg[s0].n + kBBlock - 1) / kBBlock),
+                                         seg[s0].param_index};
         }
+        written = ch.last_tile;
+        const int64_t threads = std::max<int64_t>(ch.n_params, ch.last_tile - ch.first_tile);
+        k_write_table<<<dim3(unsigned((threads + 255) / 256)), 256, 0, s>>>(entries + k0, tile_param, ch);
+        if (hipGetLastError() != hipSuccess) return LBM_EHIP;
+        k0 += ch.n_params;
     }
     BatchLaunch L{n, stride, codes8, codes, tile_records, adj, ns, f_a, f_b, n_steps,
                   p[0].flags,

@@ -147,13 +147,17 @@ struct TrtConst {
     double F[NPAIR];     // 3 w c.G for the odd member of each pair
 };
 
+// 3 w c.G for the odd member of pair k
+__host__ __device__ inline double force_term(int k, const double* force) {
+    return 3.0 * pair_weight(k) * (PCX[k] * force[0] + PCY[k] * force[1] + PCZ[k] * force[2]);
+}
+
 inline TrtConst make_trt_const(const lbm_params& p) {
     TrtConst c;
     double tau_minus = 0.5 + p.magic / (p.tau_plus - 0.5);
     c.sp = 1.0 / p.tau_plus;
     c.sm = 1.0 / tau_minus;
-    for (int k = 0; k < NPAIR; ++k)
-        c.F[k] = 3.0 * pair_weight(k) * (PCX[k] * p.force[0] + PCY[k] * p.force[1] + PCZ[k] * p.force[2]);
+    for (int k = 0; k < NPAIR; ++k) c.F[k] = force_term(k, p.force);
     return c;
 }
 

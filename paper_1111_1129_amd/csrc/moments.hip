@@ -112,7 +112,7 @@ struct MomChunk {
 };
 static_assert(sizeof(MomChunk<kMomSegs>) < 3800, "fits the kernel arguments beside the pointers");
 
-template <int ST, int SEGS>
+template <int ST, int SEGS, int POL>
 __global__ __launch_bounds__(kMomBlock) void k_moments(const typename Storage<ST>::T* __restrict__ f,
                                                        const uint32_t* __restrict__ adj,
                                                        int64_t stride, double* __restrict__ rho,
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(kMomBlock) void k_moments(const typename Storage<ST
         // flight at once
         uint32_t a[Q - 1];
 #pragma unroll
-        for (int k = 0; k < Q - 1; ++k) a[k] = ld_stream<kStream>(adj + k * stride + m);
+        for (int k = 0; k < Q - 1; ++k) a[k] = ld_stream<POL>(adj + k * stride + m);
         double g[Q];
         g[0] = static_cast<double>(f[m]);
 #pragma unroll
@@ -205,6 +205,9 @@ lbm_status launch_segments(const lbm_params* p, int64_t n, int64_t stride, const
     int64_t all_tiles = 0;
     for (int32_t k = 0; k < n_seg; ++k) all_tiles += seg_tiles(seg[k].n);
     const int64_t per = (all_tiles + target - 1) / target;  // tiles of a workgroup
+    // a state that fits the last-level cache with its list is read from there
+    const bool cached = size_t(all_tiles) * kMomBlock *
+                            (Q * sizeof(typename Storage<ST>::T) + (Q - 1) * sizeof(uint32_t)) <= kCachedBytes;
     for (int32_t k0 = 0; k0 < n_seg;) {
         MomChunk<SEGS> ch;
         ch.count = 0;
@@ -223,7 +226,8 @@ lbm_status launch_segments(const lbm_params* p, int64_t n, int64_t stride, const
             t.blocks = int32_t(b);
             blocks += b;
         }
-        k_moments<ST, SEGS><<<dim3(unsigned(blocks)), dim3(kMomBlock), 0, s>>>(
+        const auto kernel = cached ? k_moments<ST, SEGS, kCached> : k_moments<ST, SEGS, kStream>;
+        kernel<<<dim3(unsigned(blocks)), dim3(kMomBlock), 0, s>>>(
             static_cast<const typename Storage<ST>::T*>(f), adj, stride, rho, u, n,
             reduce ? partial : nullptr, ch);
         if (hipGetLastError() != hipSuccess) return LBM_EHIP;
