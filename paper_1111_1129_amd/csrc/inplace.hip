@@ -161,8 +161,10 @@ lbm_status launch_inplace(const lbm_params& p, int64_t n, int64_t stride, const 
     // cells 405 / 999 us a sweep against 427 / 1,025 with plain stores, scaled
     // FP16 232 / 598 against 248 / 616), the gather-scatter step does not mind.
     // With them both steps run forwards (backwards local steps cost 1 to 5 %).
+    SweepRule rule = kOneArray;
+    rule.nt = sizeof(T) == 8 || codes8;
     const SweepLaunch l = sweep_launch(p.flags, n, Q * sizeof(T) + (Q - 1) * (codes8 ? 1 : codes ? 2 : 4),
-                                       sizeof(T) == 8 || codes8, false);
+                                       rule);
     return with_policy(l.policy, [&](auto pol) -> lbm_status {
         const BoundKernel local(k_local<ST, PBB, pol>, l.grid, l.block, s);
         const BoundKernel scatter(codes8  ? k_gather_scatter<ST, PBB, pol, kFrom8>

@@ -363,26 +363,45 @@ __host__ __device__ inline int64_t virtual_blocks(int64_t blocks, XcdMap map) {
 //    codes 40.1 / 57.3, FP64 over 8-bit codes 38.7 / 49.3; shifted FP32 over
 //    8-bit codes at 204 MB 32.3 / 48.1; FP64 full list at 165 MB 25.9 / 32.7,
 //    at 41 MB 8.0 / 10.6).
+//  * from there to SweepRule::whole_runs the cache still holds most of it.  One
+//    run per XCD and plain stores; the two-array sweep looks at no flag and
+//    alternates its direction, so that a sweep begins with what the one before
+//    left behind (us, this form / one direction / runs of 8 tiles with
+//    nontemporal stores: FP64 full list at 345 MB 56.1 / 56.5 / 67.8, at 435 MB
+//    71.8 / 84.9 / 85.5; shifted FP32 full list at 380 MB 58.8 / 59.1 / 68.8, at
+//    433 MB 68.2 / 72.7 / 74.8; FP64 over 16-bit codes at 384 MB 69.4 / 76.2 /
+//    71.0).  The limit of the full list is 512 MiB (FP64 at 522 MB 93.7 against
+//    101.8 in runs of 8 with nontemporal stores, at 601 MB 109.2 against 106.1),
+//    of 16-bit codes 384 MiB (FP64 at 436 MB 83.3 against 80.5, scaled FP16 at
+//    448 MB 84.3 against 82.3 in runs of 8), and of 8-bit codes 256 MiB (against
+//    runs of 8 with nontemporal stores, FP64 at 265 / 303 / 404 MB 43.0 / 62.6 /
+//    80.1 and 49.2 / 59.7 / 72.5, shifted FP32 at 257 / 278 / 341 / 397 MB 41.9 /
+//    55.5 / 70.0 / 84.4 and 48.4 / 51.6 / 62.8 / 74.4, scaled FP16 at 255 / 299 /
+//    376 MB 45.8 / 66.5 / 84.8 and 53.2 / 63.3 / 77.4).
 //  * beyond it, runs of as many tiles as the LBM_FLAG_XCD_CHUNK bits say, or,
-//    without them, one run per XCD up to 384 MiB (FP64 full list, 331 MB:
-//    53.4 us against 57.8 with runs of 8 tiles) and then runs of 8 tiles: the
-//    XCDs sweep nearby parts of the list together (DRAM pages) and are evenly
-//    loaded (FP64 full list, 7.5 M cells: 525 us against 554 with an eighth
-//    each; shifted FP32 over codes, 3.6 M: 123 against 137).  Runs of 4 to 64
-//    tiles are within 1 % of it.
-//  * nontemporal stores with LBM_FLAG_NONTEMPORAL, and beyond 384 MiB also
+//    without them, of 8 tiles: the XCDs sweep nearby parts of the list together
+//    (DRAM pages) and are evenly loaded (FP64 full list, 7.5 M cells: 525 us
+//    against 554 with an eighth each; shifted FP32 over codes, 3.6 M: 123
+//    against 137).  Runs of 4 to 64 tiles are within 1 % of it.
+//  * nontemporal stores with LBM_FLAG_NONTEMPORAL, and beyond that limit also
 //    without it where they are faster nearly always: in FP64 (14 random boxes,
 //    3 orderings, full list and 16-bit codes: -7 to +0.5 %, median -3.5 %) and
 //    over 8-bit codes (narrower storages: -13 to 0 %, median -5 %).  Narrower
 //    storages over the other forms go either way (-9 to +7 %).
-//  * beyond 384 MiB with plain stores, or over 8-bit codes, every other sweep
-//    runs from the last tile to the first: it begins with what the one before
-//    left in the last-level cache.  Same boxes: plain -11 to +0.4 %, median
-//    -3.5 %; nontemporal over 8-bit codes -4 to +1 %, median -1 % (shifted FP32
-//    612 MB 113.4 -> 108.7 us, FP64 402 MB 77.4 -> 74.0); nontemporal over the
-//    other forms -1 to +2 %, so those keep one direction.
+//  * beyond that limit with plain stores, or over 8-bit codes, every other sweep
+//    runs from the last tile to the first, too.  Same boxes: plain -11 to
+//    +0.4 %, median -3.5 %; nontemporal over 8-bit codes -4 to +1 %, median -1 %
+//    (shifted FP32 612 MB 113.4 -> 108.7 us, FP64 402 MB 77.4 -> 74.0);
+//    nontemporal over the other forms -1 to +2 %, so those keep one direction.
 constexpr size_t kCachedBytes = size_t(240) << 20;
-constexpr size_t kContiguousBytes = size_t(384) << 20;
+
+struct SweepRule {
+    size_t whole_runs;  // bytes up to which an XCD takes one run
+    bool two_arrays;    // without the flags' say up to there, and alternating
+    bool nt;            // nontemporal stores beyond it also without the flag
+    bool alternate_nt;  // directions alternate with nontemporal stores too
+};
+constexpr SweepRule kOneArray = {size_t(384) << 20, false, false, false};
 
 struct SweepLaunch {
     dim3 grid, block;
@@ -401,18 +420,17 @@ struct SweepLaunch {
     }
 };
 
-// nt: nontemporal stores beyond 384 MiB also without the flag; alternate_nt:
-// directions alternate with nontemporal stores too; block: list cells per
-// workgroup (a multiple of the 256-cell tile).
-inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, bool nt,
-                                bool alternate_nt, int block = kCodeTile) {
+// block: list cells per workgroup (a multiple of the 256-cell tile).
+inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, const SweepRule& rule,
+                                int block = kCodeTile) {
     const size_t bytes = size_t(n) * cell_bytes;
     const int64_t blocks = std::max<int64_t>(1, (n + block - 1) / block);
-    const int64_t given = (flags & LBM_FLAG_XCD_CHUNK_MASK) >> LBM_FLAG_XCD_CHUNK_SHIFT;
-    const bool cached = bytes <= kCachedBytes, large = bytes > kContiguousBytes;
+    const bool cached = bytes <= kCachedBytes, large = bytes > rule.whole_runs;
+    const bool asked = large || (!cached && !rule.two_arrays);  // the flags
+    const int64_t given = asked ? (flags & LBM_FLAG_XCD_CHUNK_MASK) >> LBM_FLAG_XCD_CHUNK_SHIFT : 0;
     SweepLaunch l;
     l.blocks = uint32_t(blocks);
-    if (cached || (given == 0 && !large)) {
+    if (given == 0 && !large) {
         l.map = map_of_eighths(blocks);
     } else {
         const int64_t run = (given ? given : 8) * kCodeTile / block;
@@ -420,8 +438,9 @@ inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, boo
         while ((int64_t(2) << shift) <= run) ++shift;
         l.map = map_of_runs(shift);
     }
-    l.policy = cached ? kCached : (flags & LBM_FLAG_NONTEMPORAL) || (large && nt) ? kStreamNT : kStream;
-    l.alternate = large && (l.policy == kStream || alternate_nt);
+    const bool nt = (asked && (flags & LBM_FLAG_NONTEMPORAL)) || (large && rule.nt);
+    l.policy = cached ? kCached : nt ? kStreamNT : kStream;
+    l.alternate = !cached && (large || rule.two_arrays) && (!nt || rule.alternate_nt);
     l.grid = dim3(unsigned(virtual_blocks(blocks, l.map)));
     l.block = dim3(unsigned(block));
     return l;
@@ -432,8 +451,9 @@ inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, boo
 template <int ST>
 inline SweepLaunch two_array_launch(int32_t flags, int64_t n, size_t code_bytes, int block = kCodeTile) {
     constexpr size_t T = sizeof(typename Storage<ST>::T);
-    return sweep_launch(flags, n, 2 * Q * T + (Q - 1) * code_bytes, T == 8 || code_bytes == 1,
-                        code_bytes == 1, block);
+    const size_t whole_runs = size_t(code_bytes == 4 ? 512 : code_bytes == 2 ? 384 : 256) << 20;
+    const SweepRule rule = {whole_runs, true, T == 8 || code_bytes == 1, code_bytes == 1};
+    return sweep_launch(flags, n, 2 * Q * T + (Q - 1) * code_bytes, rule, block);
 }
 
 // Calls f(std::integral_constant<int, policy>).
