@@ -98,9 +98,9 @@ typedef enum {
 
 enum {
     /* Launch hints.  Results do not depend on them, and a state small enough to
-     * stay wholly or mostly in the last-level cache from step to step (two
-     * arrays: 256 to 512 MiB with the codes or the list that are read; one
-     * array: 240 MiB) is swept without them. */
+     * stay wholly or mostly in the last-level cache from step to step (240 to
+     * 512 MiB with the codes or the list that are read, by form) is swept
+     * without them. */
     LBM_FLAG_NONTEMPORAL = 1, /* write the new PDFs with nontemporal stores (Sec. 7);
                                  without it the library chooses by storage and size */
     LBM_FLAG_CHECK_FINITE = 2, /* lbm_moments: read the totals back (synchronising the

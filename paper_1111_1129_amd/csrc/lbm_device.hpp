@@ -397,11 +397,12 @@ constexpr size_t kCachedBytes = size_t(240) << 20;
 
 struct SweepRule {
     size_t whole_runs;  // bytes up to which an XCD takes one run
-    bool two_arrays;    // without the flags' say up to there, and alternating
+    bool hints;         // up to there the flags count, and directions don't alternate
+    bool nt_whole;      // nontemporal stores up to there, without the flag
     bool nt;            // nontemporal stores beyond it also without the flag
     bool alternate_nt;  // directions alternate with nontemporal stores too
 };
-constexpr SweepRule kOneArray = {size_t(384) << 20, false, false, false};
+constexpr SweepRule kByHints = {size_t(384) << 20, true, false, false, false};
 
 struct SweepLaunch {
     dim3 grid, block;
@@ -426,7 +427,7 @@ inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, con
     const size_t bytes = size_t(n) * cell_bytes;
     const int64_t blocks = std::max<int64_t>(1, (n + block - 1) / block);
     const bool cached = bytes <= kCachedBytes, large = bytes > rule.whole_runs;
-    const bool asked = large || (!cached && !rule.two_arrays);  // the flags
+    const bool asked = large || (!cached && rule.hints);  // the flags count
     const int64_t given = asked ? (flags & LBM_FLAG_XCD_CHUNK_MASK) >> LBM_FLAG_XCD_CHUNK_SHIFT : 0;
     SweepLaunch l;
     l.blocks = uint32_t(blocks);
@@ -438,9 +439,9 @@ inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, con
         while ((int64_t(2) << shift) <= run) ++shift;
         l.map = map_of_runs(shift);
     }
-    const bool nt = (asked && (flags & LBM_FLAG_NONTEMPORAL)) || (large && rule.nt);
+    const bool nt = (asked && (flags & LBM_FLAG_NONTEMPORAL)) || (large ? rule.nt : rule.nt_whole);
     l.policy = cached ? kCached : nt ? kStreamNT : kStream;
-    l.alternate = !cached && (large || rule.two_arrays) && (!nt || rule.alternate_nt);
+    l.alternate = !cached && (large || !rule.hints) && (!nt || rule.alternate_nt);
     l.grid = dim3(unsigned(virtual_blocks(blocks, l.map)));
     l.block = dim3(unsigned(block));
     return l;
@@ -452,7 +453,7 @@ template <int ST>
 inline SweepLaunch two_array_launch(int32_t flags, int64_t n, size_t code_bytes, int block = kCodeTile) {
     constexpr size_t T = sizeof(typename Storage<ST>::T);
     const size_t whole_runs = size_t(code_bytes == 4 ? 512 : code_bytes == 2 ? 384 : 256) << 20;
-    const SweepRule rule = {whole_runs, true, T == 8 || code_bytes == 1, code_bytes == 1};
+    const SweepRule rule = {whole_runs, false, false, T == 8 || code_bytes == 1, code_bytes == 1};
     return sweep_launch(flags, n, 2 * Q * T + (Q - 1) * code_bytes, rule, block);
 }
 
