@@ -122,7 +122,8 @@ def adjoint_gradient(lat: Lattice, prm, ns: torch.Tensor, T: int, k: int, ckpts=
     steps = _Steps(lat, prm, comp, ns)
     # states of a segment after its first, which is the checkpoint itself
     buf = [torch.empty_like(lam) for _ in range(min(k, T) - 1)] if ckpts else []
-    for s in range(len(ckpts) - 1, -1, -1):
+    # checkpoints at T and later (of a longer run) are not needed
+    for s in reversed(range(min(len(ckpts), -(-T // k)))):
         t0 = s * k
         n_seg = min(t0 + k, T) - t0
         states = [_as_state(ckpts[s], lam)] + buf[:n_seg - 1]
