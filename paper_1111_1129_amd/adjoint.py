@@ -82,13 +82,22 @@ def forward_states(lat: Lattice, prm, ns: torch.Tensor, T: int, k: int,
     cur, spare = st.f, st.g
     t = 0
     while t < T:
-        # the array that holds the state is the checkpoint (nothing writes it
-        # again); the segment goes on in two others
-        ckpts.append(cur)
         n = min(k, T - t)
-        a = torch.empty_like(cur) if spare is None else spare
-        b = torch.empty_like(cur) if n > 1 else None
-        cur, spare = steps.advance(cur, a, b, n)
+        if T <= k:
+            # one checkpoint: copied, since the state's two arrays are one
+            # allocation, which a checkpoint in it would hold whole
+            ckpts.append(cur.clone())
+            cur, spare = steps.advance(cur, spare, cur, n)
+        else:
+            # the array that holds the state is the checkpoint (nothing writes
+            # it again); the segment goes on in two others and ends in the
+            # first of them, so the second checkpoint is the second of the
+            # state's own two arrays
+            ckpts.append(cur)
+            out = torch.empty_like(cur) if spare is None else spare
+            spare = torch.empty_like(cur) if n > 1 else None
+            steps.advance(cur, *((out, spare) if n % 2 else (spare, out)), n)
+            cur = out
         t += n
     st.f, st.g = cur, torch.empty_like(cur) if spare is None else spare
     st.steps += T
@@ -207,5 +216,5 @@ class PermeabilityFn(torch.autograd.Function):
             grad = adjoint_gradient(ctx.lat, ctx.prm, ns, ctx.T, ctx.k, ctx.ckpts, ctx.comp)
         else:
             grad = adjoint_gradient_revolve(ctx.lat, ctx.prm, ns, ctx.T, ctx.snapshots, ctx.comp)
-        ctx.ckpts = None
+        ctx.ckpts = ctx.comp = None
         return (grad * gJ,) + (None,) * (ctx.n_inputs - 1)
