@@ -28,26 +28,35 @@ inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s);
 // A kernel that is launched many times in one call.  Its handle is looked up
 // once: the triple-chevron form finds it by its host address and passes the
 // launch shape through thread-local storage at every launch, which a sweep of
-// a few microseconds waits for.  The arguments are the kernel's own types.
+// a few microseconds waits for.  A handle belongs to the device that is current
+// when it is looked up, so a stream of another device (whose kernel a launch by
+// address finds) takes no handle.  The arguments are the kernel's own types.
 template <class... P>
 class BoundKernel {
 public:
     BoundKernel(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t s)
-        : grid_(grid), block_(block), stream_(s),
-          found_(hipGetFuncBySymbol(&fn_, reinterpret_cast<const void*>(kernel)) == hipSuccess) {}
+        : address_(reinterpret_cast<const void*>(kernel)), grid_(grid), block_(block), stream_(s) {
+        int current = 0;
+        hipDevice_t own = 0;
+        if (hipGetDevice(&current) != hipSuccess || hipStreamGetDevice(s, &own) != hipSuccess ||
+            own != current || hipGetFuncBySymbol(&fn_, address_) != hipSuccess)
+            fn_ = nullptr;
+    }
 
     lbm_status operator()(P... args) const {
-        if (!found_) return LBM_EHIP;
         void* ptrs[] = {static_cast<void*>(&args)...};
-        return hipModuleLaunchKernel(fn_, grid_.x, grid_.y, grid_.z, block_.x, block_.y, block_.z, 0,
-                                     stream_, ptrs, nullptr) == hipSuccess ? LBM_OK : LBM_EHIP;
+        const hipError_t e =
+            fn_ ? hipModuleLaunchKernel(fn_, grid_.x, grid_.y, grid_.z, block_.x, block_.y, block_.z, 0,
+                                        stream_, ptrs, nullptr)
+                : hipLaunchKernel(address_, grid_, block_, ptrs, 0, stream_);
+        return e == hipSuccess ? LBM_OK : LBM_EHIP;
     }
 
 private:
+    const void* address_;
     hipFunction_t fn_ = nullptr;
     dim3 grid_, block_;
     hipStream_t stream_;
-    bool found_;
 };
 
 inline bool valid_storage(int st) { return st >= LBM_F64 && st <= LBM_F16_SHIFTED_SCALED; }
