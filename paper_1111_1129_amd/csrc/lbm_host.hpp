@@ -30,7 +30,9 @@ inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s);
 // launch shape through thread-local storage at every launch, which a sweep of
 // a few microseconds waits for.  A handle belongs to the device that is current
 // when it is looked up, so a stream of another device (whose kernel a launch by
-// address finds) takes no handle.  The arguments are the kernel's own types.
+// address finds) takes no handle.  What fails is reported by the status alone:
+// HIP's last error is cleared, or the next call of the program that looks at it
+// would report it as its own.  The arguments are the kernel's own types.
 template <class... P>
 class BoundKernel {
 public:
@@ -39,8 +41,10 @@ public:
         int current = 0;
         hipDevice_t own = 0;
         if (hipGetDevice(&current) != hipSuccess || hipStreamGetDevice(s, &own) != hipSuccess ||
-            own != current || hipGetFuncBySymbol(&fn_, address_) != hipSuccess)
+            (own == current && hipGetFuncBySymbol(&fn_, address_) != hipSuccess)) {
             fn_ = nullptr;
+            (void)hipGetLastError();
+        }
     }
 
     lbm_status operator()(P... args) const {
@@ -49,7 +53,9 @@ public:
             fn_ ? hipModuleLaunchKernel(fn_, grid_.x, grid_.y, grid_.z, block_.x, block_.y, block_.z, 0,
                                         stream_, ptrs, nullptr)
                 : hipLaunchKernel(address_, grid_, block_, ptrs, 0, stream_);
-        return e == hipSuccess ? LBM_OK : LBM_EHIP;
+        if (e == hipSuccess) return LBM_OK;
+        (void)hipGetLastError();
+        return LBM_EHIP;
     }
 
 private:

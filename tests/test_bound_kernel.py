@@ -62,6 +62,16 @@ int main() {
             std::printf("device %d stream %d: status %d on %d sum %d current %d\n", cur, own, st,
                         launched_on, sum, current);
         }
+    current = 0;
+    for (int f = 0; f < 2; ++f) {
+        (f ? no_launch : no_kernel) = true;
+        for (int own = 0; own < 2; ++own) {
+            const lbm::BoundKernel k(kernel, dim3(1), dim3(1), stream(own));
+            const int st = k(1, 2l);
+            std::printf("failure %d stream %d: status %d left %d\n", f, own, st, int(hipGetLastError()));
+        }
+        no_kernel = no_launch = false;
+    }
     return 0;
 }
 """
@@ -88,3 +98,9 @@ def test_launches_on_the_device_of_its_stream(output, current, own):
     want = current if own < 0 else own
     assert (f"device {current} stream {own}: status 0 on {want} sum 42 current {current}"
             in output), "\n".join(output)
+
+
+@pytest.mark.parametrize("failure", [0, 1])  # no such kernel; the launch is refused
+@pytest.mark.parametrize("own", [0, 1])
+def test_a_failed_call_leaves_no_error_behind(output, failure, own):
+    assert f"failure {failure} stream {own}: status -5 left 0" in output, "\n".join(output)
