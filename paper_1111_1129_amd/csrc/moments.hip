@@ -287,8 +287,8 @@ lbm_status moments_call(const lbm_params* p, int32_t n_params, int64_t n, int64_
     if (!p || n_params < 1 || n_params > kMaxParamSets) return LBM_EINVAL;
     if (lbm_status st = check_layout(n, stride); st != LBM_OK) return st;
     if (!valid_segments(seg, n_seg, n, n_params)) return LBM_EINVAL;
-    // needed: one partial for every tile of the largest segment, up to what a
-    // launch of it uses; asked for: enough to launch all segments together
+    // needed: one partial for every tile of the largest segment (a launch of it
+    // uses kMomParts at most); asked for: enough to launch all segments together
     const bool segs = seg && n_seg > 0;
     int64_t largest = segs ? 0 : n, all = segs ? 0 : seg_tiles(n);
     for (int32_t k = 0; segs && k < n_seg; ++k) {
@@ -296,7 +296,7 @@ lbm_status moments_call(const lbm_params* p, int32_t n_params, int64_t n, int64_
         all += seg_tiles(seg[k].n);
     }
     const bool reduce = totals || objective;
-    const size_t need = reduce ? moments_bytes(seg_tiles(largest)) : 0;
+    const size_t need = reduce ? align_up(size_t(seg_tiles(largest)) * kPartBytes, 256) : 0;
     if (reduce && !workspace) {
         if (!ws_bytes) return LBM_EINVAL;
         *ws_bytes = std::max(need, moments_bytes(all) + (segs ? size_t(std::min<int32_t>(n_seg, kMomSegs)) * kPartBytes : 0));
