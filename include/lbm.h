@@ -97,12 +97,14 @@ typedef enum {
 } lbm_storage;
 
 enum {
-    /* Launch hints.  Results do not depend on them, and a state small enough to
-     * stay wholly or mostly in the last-level cache from step to step (240 to
-     * 512 MiB with the codes or the list that are read, by form) is swept
-     * without them. */
+    /* Launch hints.  Results do not depend on them.  Without any (neither this
+     * flag nor the XCD chunk bits) the library chooses by storage, form and size.
+     * With one it follows them, except that a call of at least 8 sweeps keeps a
+     * state of up to 240 MiB (with the codes or the list that are read) in the
+     * last-level cache and needs none; lbm_sweep_launch tells what a call uses. */
     LBM_FLAG_NONTEMPORAL = 1, /* write the new PDFs with nontemporal stores (Sec. 7);
-                                 without it the library chooses by storage and size */
+                                 large FP64 states and sweeps over 8-bit codes have
+                                 them without it too */
     LBM_FLAG_CHECK_FINITE = 2, /* lbm_moments: read the totals back (synchronising the
                                   stream) and return LBM_ENONFINITE if one is NaN or
                                   infinite (a diverged run); ignored by the sweeps */
@@ -111,7 +113,7 @@ enum {
      * workgroups so that each XCD takes k consecutive list tiles before the
      * next XCD's k.  k = 1 keeps the hardware round robin; 0 (default) lets the
      * library choose by the size of the state: one contiguous eighth of the
-     * list per XCD, or short runs.  A launch hint, like the first flag. */
+     * list per XCD, or runs of 8.  A launch hint, like the first flag. */
     LBM_FLAG_XCD_CHUNK_SHIFT = 8,
     LBM_FLAG_XCD_CHUNK_MASK = 0xff00
 };
@@ -253,6 +255,23 @@ lbm_status lbm_step(const lbm_params* p, int32_t n_params, const lbm_segment* se
                     int64_t n, int64_t stride, const uint32_t* adj, const double* ns,
                     void* f_a, void* f_b, int32_t n_steps, int32_t persistent,
                     void* workspace, size_t* ws_bytes, void* stream);
+
+/*
+ * lbm_sweep_launch -- (host) what the launch hints and the size of a state come
+ * to: how a call of n_steps sweeps over n cells is launched.  Nothing runs.
+ *
+ *  p          (host) storage and flags as in the call.
+ *  code_bytes 4 for a sweep over adj, 2 over 16-bit and 1 over 8-bit codes.
+ *  in_place   1 for lbm_step_inplace / _c8, else 0 (every two-array call).
+ *  launch     (host) int32[3]: list tiles per run of an XCD, 0 for one run of an
+ *             eighth of the list each; 0 plain accesses throughout (the state
+ *             stays in the last-level cache), 1 plain stores, 2 nontemporal
+ *             stores; 1 if every other sweep of the per-step launches runs from
+ *             the last tile to the first.
+ * Errors: LBM_EINVAL, LBM_EOVERFLOW (19 * n >= 2^32).
+ */
+lbm_status lbm_sweep_launch(const lbm_params* p, int64_t n, int32_t n_steps, int32_t code_bytes,
+                            int32_t in_place, int32_t launch[3]);
 
 /*
  * lbm_step_batch -- lbm_step (same arguments, same results bit for bit) that

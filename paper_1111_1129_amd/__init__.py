@@ -32,7 +32,7 @@ def __getattr__(name):
                 "lbm_partition_stats", "lbm_compress_adjacency", "lbm_step_c16",
                 "lbm_step_inplace", "lbm_step_adjoint_c16", "lbm_step_adjoint_c8",
                 "lbm_narrow_codes", "lbm_step_c8", "lbm_check_adjacency",
-                "lbm_step_inplace_c8", "lbm_version",
+                "lbm_step_inplace_c8", "lbm_sweep_launch", "lbm_version",
                 "LbmError"):
         from . import _native
         return getattr(_native, name)

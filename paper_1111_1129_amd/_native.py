@@ -85,6 +85,8 @@ def load(path: str = LIB_PATH):
         lib.lbm_step_batch.restype = I32
         lib.lbm_step_batch.argtypes = [C.POINTER(lbm_params), I32, P, I32, I64, I64, P, P, P, P,
                                        P, P, P, I32, I32, P, C.POINTER(SZ), P]
+        lib.lbm_sweep_launch.restype = I32
+        lib.lbm_sweep_launch.argtypes = [C.POINTER(lbm_params), I64, I32, I32, I32, P]
         lib.lbm_objective.restype = I32
         lib.lbm_objective.argtypes = [C.POINTER(lbm_params), I32, I64, I64, P, P, P, I32, P, P,
                                       C.POINTER(SZ), P]
@@ -216,6 +218,13 @@ def lbm_step(params, n, stride, adj, ns, f_a, f_b, n_steps, persistent=0,
                       stride, _ptr(adj), _ptr(ns), _ptr(f_a), _ptr(f_b), n_steps, persistent,
                       None if query else _ptr(workspace), C.byref(ws), _stream(stream))
     return st, ws.value
+
+
+def lbm_sweep_launch(params: lbm_params, n, n_steps, code_bytes=4, in_place=False):
+    """Returns (status, (tiles per run, store kind, alternating directions))."""
+    out = (C.c_int32 * 3)()
+    st = load().lbm_sweep_launch(C.byref(params), n, n_steps, code_bytes, int(in_place), out)
+    return st, tuple(out)
 
 
 def lbm_step_batch(params, n, stride, codes8, codes, tile_records, adj, ns, f_a, f_b, n_steps,

@@ -386,7 +386,7 @@ lbm_status launch_persistent_t(const BatchLaunch& L, const SweepLaunch& l, hipSt
 // A persistent workgroup takes groups of kGroupTiles tiles, a per-step one a tile.
 template <int ST, bool PBB, int SRC>
 lbm_status launch_batch_src(const BatchLaunch& L, bool persistent, hipStream_t s) {
-    const SweepLaunch l = two_array_launch<ST>(L.flags, L.n, SRC == kC8 ? 1 : SRC == kC16 ? 2 : 4,
+    const SweepLaunch l = two_array_launch<ST>(L.flags, L.n, SRC == kC8 ? 1 : SRC == kC16 ? 2 : 4, L.n_steps,
                                                persistent ? kPThreads : kBBlock);
     return with_policy(l.policy, [&](auto pol) {
         return persistent ? launch_persistent_t<ST, PBB, pol, SRC>(L, l, s)

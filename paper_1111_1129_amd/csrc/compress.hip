@@ -296,7 +296,7 @@ lbm_status launch_coded(const lbm_params& p, int64_t n, int64_t stride, const in
     T* a = static_cast<T*>(fa);
     T* b = static_cast<T*>(fb);
     const TrtConst c = make_trt_const(p);
-    const SweepLaunch l = two_array_launch<ST>(p.flags, n, codes8 ? 1 : 2);
+    const SweepLaunch l = two_array_launch<ST>(p.flags, n, codes8 ? 1 : 2, n_steps);
     return with_policy(l.policy, [&](auto pol) -> lbm_status {
         const auto steps = [&](auto&& sweep) -> lbm_status {
             for (int k = 0; k < n_steps; ++k) {

@@ -153,32 +153,9 @@ template <int ST, bool PBB>
 lbm_status launch_inplace(const lbm_params& p, int64_t n, int64_t stride, const uint32_t* adj,
                           const int16_t* codes, const int8_t* codes8, const int32_t* rec,
                           const double* ns, void* fv, int phase, int n_steps, hipStream_t s) {
-    using T = typename Storage<ST>::T;
-    T* f = static_cast<T*>(fv);
+    auto* f = static_cast<typename Storage<ST>::T*>(fv);
     const TrtConst c = make_trt_const(p);
-    // nontemporal stores without the flag in FP64 and over 8-bit codes: the local
-    // step writes whole lines that it has just read (shifted FP32 12.7 / 30.6 M
-    // cells 405 / 999 us a sweep against 427 / 1,025 with plain stores, scaled
-    // FP16 232 / 598 against 248 / 616), the gather-scatter step does not mind.
-    // With them both steps run forwards (backwards local steps cost 1 to 5 %).
-    //
-    // States somewhat larger than the last-level cache (us a sweep): over 8-bit
-    // codes always nontemporal stores and, unless the hint gives runs, one run per
-    // XCD up to 368 MiB (FP64 at 257 / 312 / 378 MB 81.8 / 100.5 / 123.6 against
-    // 88.6 / 120.7 / 139.6 with plain stores and 85.2 / 103.9 / 129.6 in runs of 8;
-    // scaled FP16 at 254 / 381 MB 82.1 / 123.6 against 86.6 / 131.0 and 86.5 /
-    // 127.5; shifted FP32 at 308 MB 93.7 against 99.4 and 92.3); over the list,
-    // whatever the hints, plain stores, one run per XCD and alternating directions
-    // up to 512 MiB (FP64 at 441 / 498 MB 117.1 / 132.0 against 125.9 / 141.2 in
-    // runs of 8 with nontemporal stores, shifted FP32 at 435 / 502 MB 88.4 / 100.7
-    // against 93.2 / 105.9 in runs of 8).
-    SweepRule rule = kByHints;
-    rule.nt = sizeof(T) == 8 || codes8;
-    rule.whole_runs = size_t(codes8 ? 368 : codes ? 384 : 512) << 20;
-    rule.hints = codes != nullptr;
-    rule.nt_whole = codes8 != nullptr;
-    const SweepLaunch l = sweep_launch(p.flags, n, Q * sizeof(T) + (Q - 1) * (codes8 ? 1 : codes ? 2 : 4),
-                                       rule);
+    const SweepLaunch l = inplace_launch<ST>(p.flags, n, codes8 ? 1 : codes ? 2 : 4, n_steps);
     return with_policy(l.policy, [&](auto pol) -> lbm_status {
         const BoundKernel local(k_local<ST, PBB, pol>, l.grid, l.block, s);
         const BoundKernel scatter(codes8  ? k_gather_scatter<ST, PBB, pol, kFrom8>

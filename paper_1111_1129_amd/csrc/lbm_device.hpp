@@ -353,18 +353,25 @@ __host__ __device__ inline int64_t virtual_blocks(int64_t blocks, XcdMap map) {
 
 // Launch of a sweep over n cells, one workgroup per 256-cell tile: the memory
 // policy and the XCD map.  They follow from the bytes that one step touches
-// (cell_bytes per cell), and the launch flags decide where both choices are
-// good somewhere:
+// (cell_bytes per cell) and from the launch hints in the flags:
 //  * up to 240 MiB the state stays in the 256 MiB last-level cache: kCached,
 //    and one run of an eighth of the blocks per XCD, so that an XCD finds the
-//    lines that it wrote itself.  The flags are not looked at: nontemporal
-//    accesses and short runs only cost here (246 MB, us a sweep, this form /
-//    nontemporal stores and loads in runs of 1 tile: scaled FP16 over 8-bit
-//    codes 40.1 / 57.3, FP64 over 8-bit codes 38.7 / 49.3; shifted FP32 over
-//    8-bit codes at 204 MB 32.3 / 48.1; FP64 full list at 165 MB 25.9 / 32.7,
-//    at 41 MB 8.0 / 10.6).
-//  * from there to SweepRule::whole_runs the cache still holds most of it.  One
-//    run per XCD and plain stores; the two-array sweep looks at no flag and
+//    lines that it wrote itself.  Nontemporal accesses and short runs only cost
+//    here (246 MB, us a sweep, this form / nontemporal stores and loads in runs
+//    of 1 tile: scaled FP16 over 8-bit codes 40.1 / 57.3, FP64 over 8-bit codes
+//    38.7 / 49.3; shifted FP32 over 8-bit codes at 204 MB 32.3 / 48.1; FP64 full
+//    list at 165 MB 25.9 / 32.7, at 41 MB 8.0 / 10.6).
+//  * that holds for a state that is swept again before others have passed
+//    through the cache.  Only the caller knows whether it is, so hints are
+//    followed in calls of fewer than 8 sweeps; from there on the call itself
+//    brings the state in (six states of 200 MiB in turn, us a sweep, hints
+//    followed / kCached, by sweeps of a call: shifted FP32 over 16-bit codes
+//    1: 38.2 / 43.2, 2: 38.0 / 42.2, 8: 35.0 / 30.9 at 180 MiB; in place over
+//    8-bit codes, runs of 16 tiles, 1: 66.6 / 73.4, 2: 55.9 / 60.9, 4: 50.7 /
+//    53.2 and 8: 50.7 / 50.8 at 180 MiB; 15 forms of 30 to 235 MiB at 8 sweeps,
+//    one state or six in turn: -31 to 0 %).
+//  * from there to SweepRule::whole_runs the cache still holds most of it.
+//    Without hints one run per XCD and plain stores; the two-array sweep
 //    alternates its direction, so that a sweep begins with what the one before
 //    left behind (us, this form / one direction / runs of 8 tiles with
 //    nontemporal stores: FP64 full list at 345 MB 56.1 / 56.5 / 67.8, at 435 MB
@@ -378,6 +385,10 @@ __host__ __device__ inline int64_t virtual_blocks(int64_t blocks, XcdMap map) {
 //    80.1 and 49.2 / 59.7 / 72.5, shifted FP32 at 257 / 278 / 341 / 397 MB 41.9 /
 //    55.5 / 70.0 / 84.4 and 48.4 / 51.6 / 62.8 / 74.4, scaled FP16 at 255 / 299 /
 //    376 MB 45.8 / 66.5 / 84.8 and 53.2 / 63.3 / 77.4).
+//    Hints are followed, whatever the call: which form is faster depends on
+//    what else passes through the cache (scaled FP16 full list at 300 MiB, one
+//    state / six in turn, hints followed 54.9 / 54.8, this form 58.5 / 73.3;
+//    FP64 full list at 450 MiB 86.9 / 86.7 and 79.2 / 93.2).
 //  * beyond it, runs of as many tiles as the LBM_FLAG_XCD_CHUNK bits say, or,
 //    without them, of 8 tiles: the XCDs sweep nearby parts of the list together
 //    (DRAM pages) and are evenly loaded (FP64 full list, 7.5 M cells: 525 us
@@ -394,21 +405,22 @@ __host__ __device__ inline int64_t virtual_blocks(int64_t blocks, XcdMap map) {
 //    (shifted FP32 612 MB 113.4 -> 108.7 us, FP64 402 MB 77.4 -> 74.0);
 //    nontemporal over the other forms -1 to +2 %, so those keep one direction.
 constexpr size_t kCachedBytes = size_t(240) << 20;
+constexpr int kResidentSweeps = 8;
 
 struct SweepRule {
-    size_t whole_runs;  // bytes up to which an XCD takes one run
-    bool hints;         // up to there the flags count, and directions don't alternate
-    bool nt_whole;      // nontemporal stores up to there, without the flag
-    bool nt;            // nontemporal stores beyond it also without the flag
-    bool alternate_nt;  // directions alternate with nontemporal stores too
+    size_t whole_runs;     // bytes up to which an XCD takes one run
+    bool alternate_whole;  // up to there directions alternate without hints
+    bool nt_whole;         // nontemporal stores up to there, without the flag
+    bool nt;               // nontemporal stores beyond it also without the flag
+    bool alternate_nt;     // directions alternate with nontemporal stores too
 };
-constexpr SweepRule kByHints = {size_t(384) << 20, true, false, false, false};
 
 struct SweepLaunch {
     dim3 grid, block;
     XcdMap map;
     int policy;
     bool alternate;  // sweeps towards the lower of two arrays run backwards
+    int32_t run;     // list tiles of a run; 0: one run per XCD
     uint32_t blocks;
 
     XcdMap towards(bool lower) const {
@@ -421,27 +433,30 @@ struct SweepLaunch {
     }
 };
 
-// block: list cells per workgroup (a multiple of the 256-cell tile).
+// n_steps: sweeps of the call; block: list cells per workgroup (a multiple of
+// the 256-cell tile).
 inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, const SweepRule& rule,
-                                int block = kCodeTile) {
+                                int n_steps, int block = kCodeTile) {
     const size_t bytes = size_t(n) * cell_bytes;
     const int64_t blocks = std::max<int64_t>(1, (n + block - 1) / block);
-    const bool cached = bytes <= kCachedBytes, large = bytes > rule.whole_runs;
-    const bool asked = large || (!cached && rule.hints);  // the flags count
-    const int64_t given = asked ? (flags & LBM_FLAG_XCD_CHUNK_MASK) >> LBM_FLAG_XCD_CHUNK_SHIFT : 0;
+    const bool hinted = flags & (LBM_FLAG_NONTEMPORAL | LBM_FLAG_XCD_CHUNK_MASK);
+    const bool cached = bytes <= kCachedBytes && (!hinted || n_steps >= kResidentSweeps);
+    const bool large = bytes > rule.whole_runs;
+    const int64_t given = cached ? 0 : (flags & LBM_FLAG_XCD_CHUNK_MASK) >> LBM_FLAG_XCD_CHUNK_SHIFT;
     SweepLaunch l;
     l.blocks = uint32_t(blocks);
-    if (given == 0 && !large) {
+    l.run = int32_t(given ? given : large ? 8 : 0);
+    if (l.run == 0) {
         l.map = map_of_eighths(blocks);
     } else {
-        const int64_t run = (given ? given : 8) * kCodeTile / block;
+        const int64_t run = int64_t(l.run) * kCodeTile / block;
         int shift = 0;
         while ((int64_t(2) << shift) <= run) ++shift;
         l.map = map_of_runs(shift);
     }
-    const bool nt = (asked && (flags & LBM_FLAG_NONTEMPORAL)) || (large ? rule.nt : rule.nt_whole);
+    const bool nt = (flags & LBM_FLAG_NONTEMPORAL) || (large ? rule.nt : rule.nt_whole);
     l.policy = cached ? kCached : nt ? kStreamNT : kStream;
-    l.alternate = !cached && (large || !rule.hints) && (!nt || rule.alternate_nt);
+    l.alternate = !cached && (large ? !nt || rule.alternate_nt : rule.alternate_whole && !hinted);
     l.grid = dim3(unsigned(virtual_blocks(blocks, l.map)));
     l.block = dim3(unsigned(block));
     return l;
@@ -450,11 +465,37 @@ inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, con
 // The two-array sweep of a storage form over the full list or 16- or 8-bit
 // codes (code_bytes 4, 2, 1).
 template <int ST>
-inline SweepLaunch two_array_launch(int32_t flags, int64_t n, size_t code_bytes, int block = kCodeTile) {
+inline SweepLaunch two_array_launch(int32_t flags, int64_t n, size_t code_bytes, int n_steps,
+                                    int block = kCodeTile) {
     constexpr size_t T = sizeof(typename Storage<ST>::T);
     const size_t whole_runs = size_t(code_bytes == 4 ? 512 : code_bytes == 2 ? 384 : 256) << 20;
-    const SweepRule rule = {whole_runs, false, false, T == 8 || code_bytes == 1, code_bytes == 1};
-    return sweep_launch(flags, n, 2 * Q * T + (Q - 1) * code_bytes, rule, block);
+    const SweepRule rule = {whole_runs, true, false, T == 8 || code_bytes == 1, code_bytes == 1};
+    return sweep_launch(flags, n, 2 * Q * T + (Q - 1) * code_bytes, rule, n_steps, block);
+}
+
+// The in-place sweep.  Nontemporal stores without the flag in FP64 and over
+// 8-bit codes: the local step writes whole lines that it has just read (shifted
+// FP32 12.7 / 30.6 M cells 405 / 999 us a sweep against 427 / 1,025 with plain
+// stores, scaled FP16 232 / 598 against 248 / 616), the gather-scatter step does
+// not mind.  With them both steps run forwards (backwards local steps cost 1 to
+// 5 %).
+//
+// States somewhat larger than the last-level cache (us a sweep): over 8-bit
+// codes always nontemporal stores and, unless the hint gives runs, one run per
+// XCD up to 368 MiB (FP64 at 257 / 312 / 378 MB 81.8 / 100.5 / 123.6 against
+// 88.6 / 120.7 / 139.6 with plain stores and 85.2 / 103.9 / 129.6 in runs of 8;
+// scaled FP16 at 254 / 381 MB 82.1 / 123.6 against 86.6 / 131.0 and 86.5 /
+// 127.5; shifted FP32 at 308 MB 93.7 against 99.4 and 92.3); over the list,
+// without hints, plain stores, one run per XCD and alternating directions up to
+// 512 MiB (FP64 at 441 / 498 MB 117.1 / 132.0 against 125.9 / 141.2 in runs of 8
+// with nontemporal stores, shifted FP32 at 435 / 502 MB 88.4 / 100.7 against
+// 93.2 / 105.9 in runs of 8).
+template <int ST>
+inline SweepLaunch inplace_launch(int32_t flags, int64_t n, size_t code_bytes, int n_steps) {
+    constexpr size_t T = sizeof(typename Storage<ST>::T);
+    const size_t whole_runs = size_t(code_bytes == 4 ? 512 : code_bytes == 2 ? 384 : 368) << 20;
+    const SweepRule rule = {whole_runs, code_bytes == 4, code_bytes == 1, T == 8 || code_bytes == 1, false};
+    return sweep_launch(flags, n, Q * T + (Q - 1) * code_bytes, rule, n_steps);
 }
 
 // Calls f(std::integral_constant<int, policy>).

@@ -94,7 +94,7 @@ lbm_status launch_steps(const lbm_params& p, int64_t n, int64_t stride, const ui
     T* a = static_cast<T*>(fa);
     T* b = static_cast<T*>(fb);
     const TrtConst c = make_trt_const(p);
-    const SweepLaunch l = two_array_launch<ST>(p.flags, n, sizeof(uint32_t));
+    const SweepLaunch l = two_array_launch<ST>(p.flags, n, sizeof(uint32_t), n_steps);
     return with_policy(l.policy, [&](auto pol) -> lbm_status {
         const BoundKernel kernel(k_trt<ST, PBB, pol>, l.grid, l.block, s);
         for (int k = 0; k < n_steps; ++k) {
@@ -114,9 +114,35 @@ lbm_status dispatch_step(const lbm_params& p, int64_t n, int64_t stride, const u
               : launch_steps<ST, false>(p, n, stride, adj, ns, fa, fb, n_steps, s);
 }
 
+template <int ST>
+SweepLaunch launch_of(const lbm_params& p, int64_t n, int n_steps, size_t code_bytes, bool in_place) {
+    return in_place ? inplace_launch<ST>(p.flags, n, code_bytes, n_steps)
+                    : two_array_launch<ST>(p.flags, n, code_bytes, n_steps);
+}
+
 }  // namespace lbm
 
 using namespace lbm;
+
+extern "C" lbm_status lbm_sweep_launch(const lbm_params* p, int64_t n, int32_t n_steps,
+                                       int32_t code_bytes, int32_t in_place, int32_t launch[3]) {
+    if (!valid_params(p) || !launch || n < 0 || n_steps < 0) return LBM_EINVAL;
+    if (code_bytes != 1 && code_bytes != 2 && code_bytes != 4) return LBM_EINVAL;
+    if (!stride_fits(n)) return LBM_EOVERFLOW;
+    const bool one = in_place != 0;
+    SweepLaunch l;
+    switch (p->storage) {
+    case LBM_F64:
+    case LBM_F64_SHIFTED: l = launch_of<LBM_F64>(*p, n, n_steps, code_bytes, one); break;
+    case LBM_F32:
+    case LBM_F32_SHIFTED: l = launch_of<LBM_F32>(*p, n, n_steps, code_bytes, one); break;
+    default: l = launch_of<LBM_F16_SHIFTED>(*p, n, n_steps, code_bytes, one); break;
+    }
+    launch[0] = l.run;
+    launch[1] = l.policy;
+    launch[2] = l.alternate;
+    return LBM_OK;
+}
 
 extern "C" lbm_status lbm_init(const lbm_params* p, int64_t n, int64_t stride, void* f,
                                double rho0, const double* u0, void* stream) {

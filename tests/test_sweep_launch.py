@@ -1,0 +1,75 @@
+"""The launch that the hints and the size of a state come to (CPU): hints are
+followed at every size, except that a call of at least 8 sweeps keeps a state of
+up to 240 MiB in the last-level cache; without hints the library chooses."""
+import pytest
+
+from paper_1111_1129_amd import _native as N
+
+MIB = 1 << 20
+EIGHTHS, CACHED, PLAIN, NONTEMPORAL = 0, 0, 1, 2
+WIDTH = {"f64": 8, "f64s": 8, "f32": 4, "f32s": 4, "f16s": 2, "f16s12": 2}
+
+
+def cells(storage, code_bytes, in_place, mib):
+    """The most cells whose state takes at most so many MiB."""
+    return mib * MIB // ((1 if in_place else 2) * 19 * WIDTH[storage] + 18 * code_bytes)
+
+
+def launch(storage, code_bytes, in_place, n, steps, nt=False, chunk=0):
+    flags = (N.FLAG_NONTEMPORAL if nt else 0) | chunk << N.FLAG_XCD_CHUNK_SHIFT
+    st, out = N.lbm_sweep_launch(N.make_params(storage=storage, flags=flags), n, steps, code_bytes,
+                                 in_place)
+    assert st == N.LBM_OK
+    return out
+
+
+FORMS = [(c, p) for c in (4, 2, 1) for p in (False, True)]
+
+
+@pytest.mark.parametrize("storage", sorted(WIDTH))
+@pytest.mark.parametrize("code_bytes,in_place", FORMS)
+def test_hints_are_followed(storage, code_bytes, in_place):
+    for mib in (1, 60, 200, 240, 241, 300, 375, 450, 511, 600, 4000):
+        n = cells(storage, code_bytes, in_place, mib)
+        for steps in (1, 2, 7, 8, 100):
+            kept = mib <= 240 and steps >= 8
+            for chunk in (1, 2, 16, 128):
+                for nt in (False, True):
+                    run, stores, alternate = launch(storage, code_bytes, in_place, n, steps, nt, chunk)
+                    assert run == (EIGHTHS if kept else chunk)
+                    if kept:
+                        assert stores == CACHED and not alternate
+                    elif nt:
+                        assert stores == NONTEMPORAL
+                    else:
+                        assert stores in (PLAIN, NONTEMPORAL)
+                    if mib <= 250:
+                        assert not alternate
+            assert launch(storage, code_bytes, in_place, n, steps, True)[1] == (
+                CACHED if kept else NONTEMPORAL)
+
+
+@pytest.mark.parametrize("storage", sorted(WIDTH))
+@pytest.mark.parametrize("code_bytes,in_place", FORMS)
+def test_without_hints_the_size_decides(storage, code_bytes, in_place):
+    n = cells(storage, code_bytes, in_place, 240)
+    for steps in (0, 1, 8):
+        assert launch(storage, code_bytes, in_place, n, steps) == (EIGHTHS, CACHED, 0)
+        assert launch(storage, code_bytes, in_place, 0, steps) == (EIGHTHS, CACHED, 0)
+        assert launch(storage, code_bytes, in_place, n + 1, steps)[1] != CACHED
+        run, stores, _ = launch(storage, code_bytes, in_place, cells(storage, code_bytes, in_place, 600),
+                                steps)
+        assert run == 8
+        assert stores == (NONTEMPORAL if WIDTH[storage] == 8 or code_bytes == 1 else PLAIN)
+
+
+def test_argument_errors():
+    ok = N.make_params()
+    bad = N.make_params(tau_plus=0.5)
+    assert N.lbm_sweep_launch(ok, 10, 1)[0] == N.LBM_OK
+    assert N.lbm_sweep_launch(bad, 10, 1)[0] == N.LBM_EINVAL
+    assert N.lbm_sweep_launch(ok, -1, 1)[0] == N.LBM_EINVAL
+    assert N.lbm_sweep_launch(ok, 10, -1)[0] == N.LBM_EINVAL
+    assert N.lbm_sweep_launch(ok, 10, 1, code_bytes=3)[0] == N.LBM_EINVAL
+    assert N.lbm_sweep_launch(ok, 1 << 32, 1)[0] == N.LBM_EOVERFLOW
+    assert N.load().lbm_sweep_launch(ok, 10, 1, 4, 0, None) == N.LBM_EINVAL
