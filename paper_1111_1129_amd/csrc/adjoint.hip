@@ -31,7 +31,7 @@ constexpr size_t kAdjCellBytes = 4 * Q * sizeof(double);
 constexpr size_t kAdjThreeWaves = size_t(5) << 28;
 
 inline SweepLaunch adjoint_launch(int32_t flags, int64_t n) {
-    constexpr SweepRule rule = {size_t(384) << 20, false, false, false, false};
+    constexpr SweepRule rule = {size_t(384) << 20, false, false, false};
     SweepLaunch l = sweep_launch(flags, n, kAdjCellBytes, rule, 1);
     l.alternate = l.alternate && size_t(n) * kAdjCellBytes > kAdjThreeWaves;
     return l;

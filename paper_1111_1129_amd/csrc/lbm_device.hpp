@@ -410,7 +410,6 @@ constexpr int kResidentSweeps = 8;
 struct SweepRule {
     size_t whole_runs;     // bytes up to which an XCD takes one run
     bool alternate_whole;  // up to there directions alternate without hints
-    bool nt_whole;         // nontemporal stores up to there, without the flag
     bool nt;               // nontemporal stores beyond it also without the flag
     bool alternate_nt;     // directions alternate with nontemporal stores too
 };
@@ -454,7 +453,7 @@ inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, con
         while ((int64_t(2) << shift) <= run) ++shift;
         l.map = map_of_runs(shift);
     }
-    const bool nt = (flags & LBM_FLAG_NONTEMPORAL) || (large ? rule.nt : rule.nt_whole);
+    const bool nt = (flags & LBM_FLAG_NONTEMPORAL) || (large && rule.nt);
     l.policy = cached ? kCached : nt ? kStreamNT : kStream;
     l.alternate = !cached && (large ? !nt || rule.alternate_nt : rule.alternate_whole && !hinted);
     l.grid = dim3(unsigned(virtual_blocks(blocks, l.map)));
@@ -469,7 +468,7 @@ inline SweepLaunch two_array_launch(int32_t flags, int64_t n, size_t code_bytes,
                                     int block = kCodeTile) {
     constexpr size_t T = sizeof(typename Storage<ST>::T);
     const size_t whole_runs = size_t(code_bytes == 4 ? 512 : code_bytes == 2 ? 384 : 256) << 20;
-    const SweepRule rule = {whole_runs, true, false, T == 8 || code_bytes == 1, code_bytes == 1};
+    const SweepRule rule = {whole_runs, true, T == 8 || code_bytes == 1, code_bytes == 1};
     return sweep_launch(flags, n, 2 * Q * T + (Q - 1) * code_bytes, rule, n_steps, block);
 }
 
@@ -480,21 +479,23 @@ inline SweepLaunch two_array_launch(int32_t flags, int64_t n, size_t code_bytes,
 // not mind.  With them both steps run forwards (backwards local steps cost 1 to
 // 5 %).
 //
-// States somewhat larger than the last-level cache (us a sweep): over 8-bit
-// codes always nontemporal stores and, unless the hint gives runs, one run per
-// XCD up to 368 MiB (FP64 at 257 / 312 / 378 MB 81.8 / 100.5 / 123.6 against
-// 88.6 / 120.7 / 139.6 with plain stores and 85.2 / 103.9 / 129.6 in runs of 8;
-// scaled FP16 at 254 / 381 MB 82.1 / 123.6 against 86.6 / 131.0 and 86.5 /
-// 127.5; shifted FP32 at 308 MB 93.7 against 99.4 and 92.3); over the list,
-// without hints, plain stores, one run per XCD and alternating directions up to
-// 512 MiB (FP64 at 441 / 498 MB 117.1 / 132.0 against 125.9 / 141.2 in runs of 8
-// with nontemporal stores, shifted FP32 at 435 / 502 MB 88.4 / 100.7 against
-// 93.2 / 105.9 in runs of 8).
+// States somewhat larger than the last-level cache, without hints (us a sweep).
+// Over 8-bit codes short runs as beyond it: one run per XCD is up to 4 % faster
+// for one state of some geometries and up to 17 % slower for others and for
+// states stepped in turn (runs of 8 / one run per XCD / plain stores and one run:
+// FP64 all-fluid box at 299 MiB 91.4 / 104.8 / 109.7 and, six in turn, 110.4 /
+// 128.7 / 116.8; FP64 packing at 308 MiB 101.7 / 107.1 / 117.1 and 116.4 / 130.9 /
+// 125.1, at 345 MiB 119.5 / 111.1 / 128.4; shifted FP32 packing at 337 MiB 108.3 /
+// 115.3 / 124.3; scaled FP16 packing at 294 MiB 100.9 / 96.7 / 136.7 and 107.3 /
+// 107.3 / 140.9).  Over the list plain stores, one run per XCD and alternating
+// directions up to 512 MiB (FP64 at 441 / 498 MB 117.1 / 132.0 against 125.9 /
+// 141.2 in runs of 8 with nontemporal stores, shifted FP32 at 435 / 502 MB 88.4 /
+// 100.7 against 93.2 / 105.9 in runs of 8).
 template <int ST>
 inline SweepLaunch inplace_launch(int32_t flags, int64_t n, size_t code_bytes, int n_steps) {
     constexpr size_t T = sizeof(typename Storage<ST>::T);
-    const size_t whole_runs = size_t(code_bytes == 4 ? 512 : code_bytes == 2 ? 384 : 368) << 20;
-    const SweepRule rule = {whole_runs, code_bytes == 4, code_bytes == 1, T == 8 || code_bytes == 1, false};
+    const size_t whole_runs = size_t(code_bytes == 4 ? 512 : code_bytes == 2 ? 384 : 240) << 20;
+    const SweepRule rule = {whole_runs, code_bytes == 4, T == 8 || code_bytes == 1, false};
     return sweep_launch(flags, n, Q * T + (Q - 1) * code_bytes, rule, n_steps);
 }
 

@@ -63,6 +63,14 @@ def test_without_hints_the_size_decides(storage, code_bytes, in_place):
         assert stores == (NONTEMPORAL if WIDTH[storage] == 8 or code_bytes == 1 else PLAIN)
 
 
+@pytest.mark.parametrize("storage", sorted(WIDTH))
+def test_in_place_over_8_bit_codes_takes_short_runs_beyond_the_cache(storage):
+    for mib in (241, 300, 368, 600):
+        n = cells(storage, 1, True, mib)
+        assert launch(storage, 1, True, n, 1) == (8, NONTEMPORAL, 0)
+        assert launch(storage, 1, True, n, 10, nt=True) == (8, NONTEMPORAL, 0)
+
+
 def test_argument_errors():
     ok = N.make_params()
     bad = N.make_params(tau_plus=0.5)
