@@ -25,29 +25,32 @@ constexpr int kAdjBlock = 256;
 // Bytes per cell (sweep_launch): lambda^{t+1}, lambda^t, and f_t twice, since
 // every step of the reverse sweep reads another state.
 constexpr size_t kAdjCellBytes = 4 * Q * sizeof(double);
-// Up to here the kernels are built for three waves per SIMD; beyond it steps
-// with plain stores alternate their direction (8-bit codes, 2.9 / 4.0 / 7.8 M
-// cells 288 / 396 / 780 -> 278 / 387 / 771 us; 2.0 M cells 193 -> 195).
-constexpr size_t kAdjThreeWaves = size_t(5) << 28;
 
+// Beyond 384 MiB steps with plain stores alternate their direction (8-bit codes,
+// 0.96 / 1.5 / 2.0 / 3.3 / 7.8 M cells 87.6 / 157.8 / 194.9 / 332.9 / 771 -> 84.4 /
+// 147.9 / 182.1 / 323.7 / 766 us).
 inline SweepLaunch adjoint_launch(int32_t flags, int64_t n) {
     constexpr SweepRule rule = {size_t(384) << 20, false, false, false};
-    SweepLaunch l = sweep_launch(flags, n, kAdjCellBytes, rule, 1);
-    l.alternate = l.alternate && size_t(n) * kAdjCellBytes > kAdjThreeWaves;
-    return l;
+    return sweep_launch(flags, n, kAdjCellBytes, rule, 1);
 }
 
 // Waves per SIMD that the kernels are built for.  A cell holds 38 gathered and
 // read values in FP64, and the compiler takes 188 registers (two waves) unless
 // told to fit three (168, nothing spilled; four would spill 46).  Three waves
-// up to the same size: 0.35 / 0.85 / 2.0 M cells over 8-bit codes 29.6 / 70.6 /
-// 190.0 us against 32.5 / 76.5 / 192.3 with two, but 7.8 M cells 782 against
-// 771 and with nontemporal stores 823 against 797.
+// keep more loads in flight, two leave more of the caches to each: 8-bit codes, us
+// with three / two waves, plain stores 0.20 / 0.96 / 1.5 / 2.0 / 2.1 M cells 19.6 /
+// 21.9, 84.4 / 89.4, 147.9 / 150.7, 182.1 / 185.4, 205.0 / 205.0, then within 1 %
+// of each other to 4 M and 768 / 763 at 7.8 M; nontemporal stores 0.96 / 1.5 / 1.76 /
+// 1.94 / 2.1 / 4.9 M 101.1 / 102.7, 171.0 / 172.7, 185.2 / 181.0, 200.5 / 195.7,
+// 233.2 / 226.3, 533 / 518.
+constexpr size_t kAdjThreeWaves = size_t(1280) << 20, kAdjThreeWavesNT = size_t(960) << 20;
+
 template <class F>
 lbm_status with_policy_waves(int policy, int64_t n, F&& f) {
     return with_policy(policy, [&](auto pol) {
-        return size_t(n) * kAdjCellBytes <= kAdjThreeWaves ? f(pol, std::integral_constant<int, 3>{})
-                                                      : f(pol, std::integral_constant<int, 2>{});
+        constexpr size_t three = pol == kStreamNT ? kAdjThreeWavesNT : kAdjThreeWaves;
+        return size_t(n) * kAdjCellBytes <= three ? f(pol, std::integral_constant<int, 3>{})
+                                                  : f(pol, std::integral_constant<int, 2>{});
     });
 }
 static_assert(kAdjBlock == kCodeTile, "a workgroup of k_adjoint_coded is one code tile");
