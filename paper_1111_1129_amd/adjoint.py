@@ -30,6 +30,7 @@ class _Steps:
     is resolved once: a small box is stepped as fast as its calls are issued."""
 
     def __init__(self, lat: Lattice, prm, comp: Compressed, ns: torch.Tensor | None):
+        assert comp.n == lat.base + lat.n_fluid and comp.codes.shape[1] == lat.stride
         lib = N.load()
         self.keep = (lat, prm, comp, ns)
         head = (C.byref(prm), lat.n_fluid, lat.stride, comp.codes8.data_ptr(),
