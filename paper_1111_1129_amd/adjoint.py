@@ -30,7 +30,6 @@ class _Steps:
     is resolved once: a small box is stepped as fast as its calls are issued."""
 
     def __init__(self, lat: Lattice, prm, comp: Compressed, ns: torch.Tensor | None):
-        assert comp.n == lat.base + lat.n_fluid and comp.codes.shape[1] == lat.stride
         lib = N.load()
         self.keep = (lat, prm, comp, ns)
         head = (C.byref(prm), lat.n_fluid, lat.stride, comp.codes8.data_ptr(),
@@ -77,6 +76,7 @@ def forward_states(lat: Lattice, prm, ns: torch.Tensor, T: int, k: int,
     the 16-bit codes elsewhere (bitwise the same states as the sweep over the
     full list, fewer bytes)."""
     comp = codes_of(lat, comp)
+    assert comp.n == lat.base + lat.n_fluid and comp.codes.shape[1] == lat.stride
     st = init(lat, prm, ns=ns)
     steps = _Steps(lat, prm, comp, ns)
     ckpts = []

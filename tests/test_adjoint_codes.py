@@ -1,4 +1,4 @@
-"""The adjoint's runs take the codes of their own list only (CPU: refused before
+"""A forward run takes the codes of its own list only (CPU: refused before
 anything is launched)."""
 import pytest
 import torch
@@ -19,4 +19,4 @@ def test_codes_of_another_list_are_refused(n, stride):
                     torch.zeros((18, 320), dtype=torch.int32))
     prm = L.params(storage="f64s")
     with pytest.raises(AssertionError):
-        AD._Steps(lat, prm, arrays(n, stride), None)
+        AD.forward_states(lat, prm, None, 2, 1, arrays(n, stride))
