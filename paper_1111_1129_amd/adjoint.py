@@ -25,14 +25,14 @@ from .lattice import Compressed, Lattice, compress, init, narrow, objective
 
 
 class _Steps:
-    """Sweeps and adjoint steps of one lattice over its codes, on the stream
-    that is current when this is made.  What does not change from call to call
+    """Sweeps and adjoint steps over the first n cells of a list and its codes,
+    on the stream that is current when this is made.  What does not change from call to call
     is resolved once: a small box is stepped as fast as its calls are issued."""
 
-    def __init__(self, lat: Lattice, prm, comp: Compressed, ns: torch.Tensor | None):
+    def __init__(self, lat: Lattice, n: int, prm, comp: Compressed, ns: torch.Tensor | None):
         lib = N.load()
         self.keep = (lat, prm, comp, ns)
-        head = (C.byref(prm), lat.n_fluid, lat.stride, comp.codes8.data_ptr(),
+        head = (C.byref(prm), n, lat.stride, comp.codes8.data_ptr(),
                 comp.codes.data_ptr(), comp.tile_records.data_ptr(), lat.adj.data_ptr())
         ns_ptr, stream = N._ptr(ns), N._stream()
         step, adjoint = lib.lbm_step_c8, lib.lbm_step_adjoint_c8
@@ -78,7 +78,7 @@ def forward_states(lat: Lattice, prm, ns: torch.Tensor, T: int, k: int,
     comp = codes_of(lat, comp)
     assert comp.n == lat.base + lat.n_fluid and comp.codes.shape[1] == lat.stride
     st = init(lat, prm, ns=ns)
-    steps = _Steps(lat, prm, comp, ns)
+    steps = _Steps(lat, st.n, prm, comp, ns)
     ckpts = []
     cur, spare = st.f, st.g
     t = 0
@@ -129,7 +129,7 @@ def adjoint_gradient(lat: Lattice, prm, ns: torch.Tensor, T: int, k: int, ckpts=
     lam_prev = torch.empty_like(lam)
     grad = torch.zeros(S, dtype=torch.float64, device=dev)
     N._check("lbm_step_adjoint", N.lbm_step_adjoint(prm, n, S, lat.adj, None, ns, None, lam, None))
-    steps = _Steps(lat, prm, comp, ns)
+    steps = _Steps(lat, n, prm, comp, ns)
     # states of a segment after its first, which is the checkpoint itself
     buf = [torch.empty_like(lam) for _ in range(min(k, T) - 1)] if ckpts else []
     # checkpoints at T and later (of a longer run) are not needed
@@ -166,7 +166,7 @@ def adjoint_gradient_revolve(lat: Lattice, prm, ns: torch.Tensor, T: int, snapsh
     N._check("lbm_step_adjoint", N.lbm_step_adjoint(prm, n, S, lat.adj, None, ns, None, lam, None))
     lams = [lam, lam_prev]
     swept = [0]
-    steps = _Steps(lat, prm, comp, ns)
+    steps = _Steps(lat, n, prm, comp, ns)
 
     def advance(src, dst, t, k):
         # no copy: the sweeps after the first alternate between slot dst and

@@ -1,0 +1,35 @@
+"""forward_states over a list whose geometry begins at a later column: all listed
+cells are swept, those before it too."""
+import pytest
+import torch
+
+from paper_1111_1129_amd import adjoint as AD
+from paper_1111_1129_amd import inputs as I
+from paper_1111_1129_amd import lattice as L
+
+from gpu_helpers import dev_flags, print_case
+
+pytestmark = pytest.mark.gpu
+
+
+def two_in_one():
+    a, b = (I.random_flags(s, 14, 9, 11, 0.8, periodic=1) for s in (3, 4))
+    na, nb = (L.count_fluid(dev_flags(g), 1) for g in (a, b))
+    first = L.build(dev_flags(a), 1, stride=L.aligned_stride(na + nb))
+    return L.build(dev_flags(b), 1, base=na, stride=first.stride, adj=first.adj)
+
+
+@pytest.mark.parametrize("T,k", [(1, 1), (4, 2), (5, 5), (7, 3)])
+def test_states_of_a_list_that_begins_later(T, k):
+    print_case("forward states, base > 0", T, k)
+    lat = two_in_one()
+    n = lat.base + lat.n_fluid
+    prm = L.params(0.8, 3 / 16, (1e-4, 0, 0), "f64s")
+    J, ckpts, st = AD.forward_states(lat, prm, None, T, k)
+    plain = L.init(lat, prm)
+    for t in range(T):
+        if t % k == 0:
+            assert torch.equal(ckpts[t // k][:, :n], plain.f[:, :n])
+        L.step(plain, 1)
+    assert torch.equal(st.f[:, :n], plain.f[:, :n])
+    assert J.item() == L.objective(plain)[0].item()
