@@ -78,7 +78,7 @@ def forward_states(lat: Lattice, prm, ns: torch.Tensor, T: int, k: int,
     comp = codes_of(lat, comp)
     assert comp.n == lat.base + lat.n_fluid and comp.codes.shape[1] == lat.stride
     st = init(lat, prm, ns=ns)
-    steps = _Steps(lat, st.n, prm, comp, ns)
+    steps = _Steps(lat, st.n, st.first_params, comp, ns)
     ckpts = []
     cur, spare = st.f, st.g
     t = 0

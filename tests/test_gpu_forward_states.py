@@ -1,5 +1,5 @@
-"""forward_states over a list whose geometry begins at a later column: all listed
-cells are swept, those before it too."""
+"""forward_states over a list whose geometry begins at a later column (all listed
+cells are swept, those before it too) and with a list of parameter sets."""
 import pytest
 import torch
 
@@ -33,3 +33,15 @@ def test_states_of_a_list_that_begins_later(T, k):
         L.step(plain, 1)
     assert torch.equal(st.f[:, :n], plain.f[:, :n])
     assert J.item() == L.objective(plain)[0].item()
+
+
+def test_a_list_of_parameter_sets():
+    print_case("forward states, parameter list")
+    lat = two_in_one()
+    n = lat.base + lat.n_fluid
+    prm = L.params(0.8, 3 / 16, (1e-4, 0, 0), "f64s")
+    other = L.params(0.7, 3 / 16, (2e-4, 0, 0), "f64s")
+    J, ckpts, st = AD.forward_states(lat, [prm, other], None, 3, 2)
+    J1, ckpts1, st1 = AD.forward_states(lat, prm, None, 3, 2)
+    assert J.item() == J1.item() and len(ckpts) == len(ckpts1)
+    assert torch.equal(st.f[:, :n], st1.f[:, :n])
