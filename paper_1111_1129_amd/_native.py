@@ -24,6 +24,7 @@ STORAGES = {"f64": 0, "f64s": 1, "f32": 2, "f32s": 3, "f16s": 4, "f16s12": 5}
 STORAGE_DTYPE = {0: torch.float64, 1: torch.float64, 2: torch.float32, 3: torch.float32,
                  4: torch.float16, 5: torch.float16}  # 5 holds 2^12 (f - w) as FP16
 F16_SCALE = 4096.0  # factor of the scaled shifted FP16 storage
+NONTEMPORAL_STORES = 2  # store kind of lbm_sweep_launch
 FLAG_NONTEMPORAL = 1
 FLAG_CHECK_FINITE = 2
 FLAG_XCD_CHUNK_SHIFT = 8
@@ -34,7 +35,7 @@ ENTRY_POINTS = ("lbm_build_adjacency", "lbm_init", "lbm_step", "lbm_step_batch",
                 "lbm_partition_stats", "lbm_compress_adjacency", "lbm_step_c16",
                 "lbm_step_inplace", "lbm_step_adjoint_c16", "lbm_step_adjoint_c8",
                 "lbm_narrow_codes", "lbm_step_c8", "lbm_step_inplace_c8", "lbm_check_adjacency",
-                "lbm_version", "lbm_status_string")
+                "lbm_sweep_launch", "lbm_version", "lbm_status_string")
 
 
 class lbm_geom(C.Structure):

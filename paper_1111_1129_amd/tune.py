@@ -6,8 +6,8 @@ sweep's sustained HBM bandwidth also depends on where the 19 + 19 PDF rows
 and the 18 adjacency rows fall in the HBM channel interleave (set by the row
 stride) and on the store policy, so those are tuned the same way: a handful
 of candidate strides (all 128-byte aligned) x {plain, nontemporal stores} x
-a few workgroup-to-XCD chunk lengths are each timed over a few sweeps, and
-the fastest is kept.  Results do not depend on the choice (the
+a few workgroup-to-XCD chunk lengths are each timed over a few sweeps, as far as
+they come to different launches, and the fastest is kept.  Results do not depend on the choice (the
 arithmetic per cell is identical); only the speed does.
 """
 from __future__ import annotations
@@ -16,6 +16,7 @@ import dataclasses
 
 import torch
 
+from . import _native as N
 from . import lattice as L
 
 
@@ -44,6 +45,23 @@ def candidate_strides(n: int) -> list[int]:
 
 
 SWEEPS = ("full", "c16", "c8", "inplace", "inplace_c16", "inplace_c8")
+
+
+def launch_options(n: int, storage: str, kind: str = "full", chunks=(1, 4, 16, 64, 0)) -> list:
+    """The (nontemporal, xcd_chunk) options that come to different launches of
+    n cells in calls of many sweeps, one of each: the one without hints where it
+    is among equals, and nontemporal where the launch's stores are."""
+    code_bytes = 1 if kind.endswith("c8") else 2 if kind.endswith("c16") else 4
+    kept = {}
+    for chunk in sorted(chunks):
+        for nt in (False, True):
+            st, launch = N.lbm_sweep_launch(L.params(storage=storage, nontemporal=nt, xcd_chunk=chunk),
+                                            n, 100, code_bytes, kind.startswith("inplace"))
+            N._check("lbm_sweep_launch", st)
+            known = kept.get(launch)
+            if known is None or (launch[1] == N.NONTEMPORAL_STORES and nt and not known[0]):
+                kept[launch] = (nt, chunk)
+    return list(kept.values())
 
 
 class Sweeper:
@@ -97,7 +115,8 @@ def tune_layout(flags: torch.Tensor, periodic: int, order: str = "lex", param: i
     """Time the candidate layouts on this geometry and return the fastest.
 
     `sweep` names the sweep being tuned (see Sweeper); timed runs use an even
-    number of sweeps.
+    number of sweeps.  Of the options that come to one launch (all of them, for
+    a state that stays in the last-level cache) one is timed.
 
     Two stages: every candidate is timed over `sweeps` sweeps; the best
     configuration of every stride and the best `finalists` overall are timed
@@ -115,11 +134,10 @@ def tune_layout(flags: torch.Tensor, periodic: int, order: str = "lex", param: i
     stream = torch.cuda.current_stream()
     for S in cands:
         sw = Sweeper(L.build(flags, periodic, order, param, stride=S), sweep)
-        for nt in (False, True):
-            for chunk in chunks:
-                prm = L.params(0.8, 3.0 / 16.0, force, storage, nontemporal=nt, xcd_chunk=chunk)
-                t = _time_sweeps(sw.lat, prm, sweeps, stream, sw)
-                table.append((S, nt, chunk, round(n / t / 1e6, 1)))
+        for nt, chunk in launch_options(n, storage, sweep, chunks):
+            prm = L.params(0.8, 3.0 / 16.0, force, storage, nontemporal=nt, xcd_chunk=chunk)
+            t = _time_sweeps(sw.lat, prm, sweeps, stream, sw)
+            table.append((S, nt, chunk, round(n / t / 1e6, 1)))
         del sw
     ranked = sorted(table, key=lambda r: -r[3])
     top = ranked[:max(1, finalists)]
@@ -223,21 +241,20 @@ def tune_batch_layout(flags_list, periodic_list, order: str = "lex", param: int 
     best, table = None, []
     for S in candidate_strides(total):
         batch = L.Batch(flags_list, periodic_list, order, param, stride=S, counts=counts)
-        for nt in (False, True):
-            for chunk in chunks:
-                prm = L.params(0.8, 3.0 / 16.0, force, storage, nontemporal=nt, xcd_chunk=chunk)
-                st = batch.init(prm)
-                L.step(st, 2)
-                e0 = torch.cuda.Event(enable_timing=True)
-                e1 = torch.cuda.Event(enable_timing=True)
-                e0.record(stream)
-                L.step(st, sweeps)
-                e1.record(stream)
-                e1.synchronize()
-                rate = total * sweeps / (e0.elapsed_time(e1) / 1e3) / 1e6
-                table.append((S, nt, chunk, round(rate, 1)))
-                if best is None or rate > best[3]:
-                    best = (S, nt, chunk, rate)
-                del st
+        for nt, chunk in launch_options(total, storage, "full", chunks):
+            prm = L.params(0.8, 3.0 / 16.0, force, storage, nontemporal=nt, xcd_chunk=chunk)
+            st = batch.init(prm)
+            L.step(st, 2)
+            e0 = torch.cuda.Event(enable_timing=True)
+            e1 = torch.cuda.Event(enable_timing=True)
+            e0.record(stream)
+            L.step(st, sweeps)
+            e1.record(stream)
+            e1.synchronize()
+            rate = total * sweeps / (e0.elapsed_time(e1) / 1e3) / 1e6
+            table.append((S, nt, chunk, round(rate, 1)))
+            if best is None or rate > best[3]:
+                best = (S, nt, chunk, rate)
+            del st
         del batch
     return best[0], best[1], best[2], table
