@@ -15,6 +15,9 @@
 //              fluid lanes before it (mbcnt over the ballot mask); write
 //              cell_of[rank] and index_of[cell];
 //   4. adjacency: one thread per fluid cell, 18 neighbour lookups in index_of.
+// A large lexicographic list (kTableBox) looks its neighbours up in rank words,
+// a bit mask and a rank for every 32 cells: pass 3 writes those and cell_of, and
+// index_of is written by another walk after the adjacency, if the caller wants it.
 // All counts are exact integers, so the result does not depend on tile size
 // or workgroup count (Sec. 8: the same sparse representation always).
 //
@@ -525,7 +528,8 @@ struct RankWord {
 };
 constexpr int64_t kRankGuard = 2;
 
-inline int64_t rank_words(int64_t units) { return 1 + units * (kUnit / 32) + kRankGuard; }
+// Entries of a table over so many units: a guard, the words, two more guards.
+constexpr int64_t rank_words(int64_t units) { return 1 + units * (kUnit / 32) + kRankGuard; }
 
 // Smallest box for the rank words: below it index_of stays in the last-level
 // cache between the two kernels, and reading it costs less than a second pass
@@ -533,8 +537,8 @@ inline int64_t rank_words(int64_t units) { return 1 + units * (kUnit / 32) + kRa
 // porosity 0.8, 426 / 452; 384^3 634 / 460 and 1,084 / 765).  The words fit in
 // the index: a quarter of it, and a unit's worth and the guards beyond that.
 constexpr int64_t kTableBox = int64_t(40) << 20;
-static_assert((kTableBox / 32 + kUnit / 32 + 1 + kRankGuard) * sizeof(RankWord) <=
-              kTableBox * sizeof(int32_t), "rank words fit in the index");
+static_assert(rank_words(kTableBox / kUnit + 1) * sizeof(RankWord) <= kTableBox * sizeof(int32_t),
+              "rank words fit in the index");
 
 // Which of its results a k_emit launch writes: the list and the index, the list
 // and the rank words, or the index.
@@ -549,7 +553,7 @@ __global__ __launch_bounds__(kWalkBlock) void k_emit(KeySpace ks, const uint8_t*
                                                      RankWord* __restrict__ table) {
     const uint32_t g = wave_group();
     if (PART == kEmitList && g == 0 && threadIdx.x <= kRankGuard)
-        table[threadIdx.x == 0 ? 0 : int64_t(units) * (kUnit / 32) + threadIdx.x] = RankWord{0u, 0u};
+        table[threadIdx.x == 0 ? 0 : rank_words(units) - threadIdx.x] = RankWord{0u, 0u};
     if (g >= groups) return;
     const int lane = int(threadIdx.x) & 63;
     uint32_t r = group_offset[g];
@@ -733,7 +737,6 @@ static int feistel_half_bits(uint64_t n_box) {
     return h;
 }
 
-// Fills ks; returns LBM_OK or an error for unusable geometry/order.
 // Divisors of the blocked order with block edge b.  A slab or row that is
 // larger than the box never divides anything: its quotient is 0 for every
 // position, which any divisor above the last position gives.
@@ -767,6 +770,7 @@ static BlockDivs make_blocks(const lbm_geom& g, int64_t b) {
     return d;
 }
 
+// Fills ks; returns LBM_OK or an error for unusable geometry/order.
 static lbm_status make_keyspace(const lbm_geom& g, KeySpace& ks) {
     ks = KeySpace{};
     ks.order = g.order;
@@ -914,6 +918,6 @@ extern "C" lbm_status lbm_build_adjacency(const lbm_geom* g, const uint8_t* flag
             k_adjacency<false><<<grid, dim3(256), 0, s>>>(cell_of, FromTable{table}, nf, ag, map, adj);
         if (hipGetLastError() != hipSuccess) return LBM_EHIP;
     }
-    if (table) return emit(lex, std::integral_constant<int, kEmitIndex>{});
+    if (table && index_of) return emit(lex, std::integral_constant<int, kEmitIndex>{});
     return LBM_OK;
 }
