@@ -35,75 +35,117 @@ namespace lbm {
 constexpr int kCTile = kCodeTile;  // cells per tile = workgroup size of the sweep
 constexpr int kRec = kCodeRec;
 
-// Smallest / largest of a value over the wave, uniform.
-__device__ __forceinline__ int32_t wave_max(int32_t v) {
-#define LBM_DPP_MAX(ctrl) v = max(v, __builtin_amdgcn_update_dpp(v, v, ctrl, 0xf, 0xf, false))
-    LBM_DPP_MAX(0xB1);   // exchange neighbours, pairs, halves of 8, halves of a row of 16
-    LBM_DPP_MAX(0x4E);
-    LBM_DPP_MAX(0x141);
-    LBM_DPP_MAX(0x140);
-    LBM_DPP_MAX(0x142);  // lane 15 of a row to the next row, lane 31 to the upper half
-    LBM_DPP_MAX(0x143);
-#undef LBM_DPP_MAX
-    return __builtin_amdgcn_readlane(v, 63);
-}
-
-// Four consecutive elements of a row at p: one access with VEC, else four.
-template <bool VEC, class T>
-__device__ __forceinline__ void load4(const T* p, T* v) {
-    typedef T V4 __attribute__((ext_vector_type(4)));
-    if constexpr (VEC) {
-        const V4 q = *reinterpret_cast<const V4*>(p);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = q[j];
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = p[j];
-    }
-}
-
-// ... the first `live` of them stored
-template <bool VEC, class T>
-__device__ __forceinline__ void store4(T* p, const T* v, int live) {
-    typedef T V4 __attribute__((ext_vector_type(4)));
-    if (VEC && live == 4) {
-        *reinterpret_cast<V4*>(p) = V4{v[0], v[1], v[2], v[3]};
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (j < live) p[j] = v[j];
-    }
-}
-
-// The code kernels take one wave per tile and four consecutive cells per lane.
-// They stream whole rows, and what bounds them is the number of memory
-// instructions: with one cell per lane a wave moved 64 to 256 bytes with each.
-// 30.6 M cells, one cell per lane -> four: k_compress (108 bytes per cell) 793
-// -> 616 us, 5.3 TB/s, its tile minima by wave shifts instead of through LDS;
-// k_narrow (54 bytes) 317 -> 306 us.  4.8 M cells: 158 -> 111, 52 -> 48 us.
-// VEC: rows start on a multiple of four elements of an aligned array.
-struct LaneCells {
-    int64_t m;  // first cell; lanes past the list take cells 0.. and are ignored
-    int live;   // cells of this lane in the list
-};
-
-__device__ __forceinline__ LaneCells lane_cells(int64_t tile, int lane, int64_t n) {
-    const int64_t m = tile * kCTile + 4 * lane;
-    return LaneCells{m < n ? m : 0, int(m < n ? (n - m < 4 ? n - m : 4) : 0)};
-}
-
+// The code kernels take one wave per tile and four consecutive cells per lane:
+// they stream whole rows, and with one cell per lane a wave moves 64 to 256
+// bytes with each memory instruction.  Rows may begin anywhere (a row stride or
+// an array of the caller's): the accesses ask for an element's alignment only.
+// Small lists give a SIMD one wave or none, which then waits for its own
+// instructions, so these are few and without branches: values that neither the
+// largest nor the smallest sees instead of conditions, 16-bit pairs in one
+// operation, and reductions in which four directions share the lanes.
+// us over random boxes of 2.4 k / 0.53 M / 10 M / 34 M cells: k_compress (108
+// bytes per cell) 5.3 / 12.6 / 199 / 668 against 6.9 / 21.6 / 250 / 835 with one
+// cell per lane, and 5.3 / 13.2 / 226 / 761 against 7.1 / 21.5 / 257 / 842 where
+// rows begin off their vectors; k_narrow (54 bytes) 4.0 / 7.3 / 96 / 315 against
+// 3.2 / 7.8 / 96 / 332, off their vectors 3.8 / 7.8 / 112 / 374 against 3.4 / 8.4 /
+// 127 / 442.
 constexpr int kCodeBlock = 256;  // 4 waves, 4 tiles
 
-inline bool rows_of_4(int64_t stride, const void* p, size_t element) {
-    return stride % 4 == 0 && reinterpret_cast<uintptr_t>(p) % (4 * element) == 0;
-}
+// LDS that a launch asks for and nothing uses: it holds lists that the caches
+// cannot hold to two workgroups per CU.  Five to seven spread the rows that are
+// read and written together over more places of the memory (k_compress / k_narrow
+// with two and with all that fit: 30.6 M cells of a packing 639 / 299 and 658 /
+// 327 us, 10 M of a random box 199 / 96 and 206 / 103; but 4.2 M 89 / 45.5 and
+// 90 / 44.4, 1.3 M 23.8 / 13.8 and 23.4 / 12.5).
+constexpr int64_t kCodeStreamCells = int64_t(8) << 20;
+inline unsigned code_lds(int64_t n) { return n > kCodeStreamCells ? 64u << 10 : 0u; }
+
+typedef int16_t Pair __attribute__((ext_vector_type(2)));
+
+// Four elements, and the same at any element's address.
+template <class T> struct Four {
+    typedef T V __attribute__((ext_vector_type(4)));
+    typedef V Any __attribute__((aligned(alignof(T))));
+};
+using Slots4 = Four<uint32_t>::V;
+using Codes4 = Four<int16_t>::V;
+using Bytes4 = Four<int8_t>::V;
+
+// The four cells of a lane.
+struct LaneCells {
+    int64_t m;    // first cell
+    int64_t n;    // cells of the list
+    bool whole;   // the tile's 256 cells are all in the list (uniform)
+    __device__ __forceinline__ LaneCells(int64_t tile, int lane, int64_t cells)
+        : m(tile * kCTile + 4 * lane), n(cells), whole((tile + 1) * kCTile <= cells) {}
+};
 
 __device__ __forceinline__ int64_t wave_tile() {
     return int64_t(blockIdx.x) * (kCodeBlock / 64) +
            __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
 }
 
-template <bool VEC>
+// Four consecutive entries of every row of [18][stride] at a lane's cells;
+// `none` in place of cells past the list (which read cell 0: no branches
+// between the loads of the last tile, which a list of a few tiles waits for).
+template <class T>
+__device__ __forceinline__ void load_rows(const T* __restrict__ rows, int64_t stride, LaneCells c, T none,
+                                          typename Four<T>::V* v) {
+    if (c.whole) {
+#pragma unroll
+        for (int k = 0; k < Q - 1; ++k)
+            v[k] = *reinterpret_cast<const typename Four<T>::Any*>(rows + k * stride + c.m);
+    } else {
+#pragma unroll
+        for (int k = 0; k < Q - 1; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool live = c.m + j < c.n;
+                const T x = rows[k * stride + (live ? c.m + j : 0)];
+                v[k][j] = live ? x : none;
+            }
+    }
+}
+
+template <class T>
+__device__ __forceinline__ void store_rows(T* __restrict__ rows, int64_t stride, LaneCells c,
+                                           const typename Four<T>::V* v) {
+    if (c.whole) {
+#pragma unroll
+        for (int k = 0; k < Q - 1; ++k)
+            *reinterpret_cast<typename Four<T>::Any*>(rows + k * stride + c.m) = v[k];
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (c.m + j < c.n) {
+#pragma unroll
+                for (int k = 0; k < Q - 1; ++k) rows[k * stride + c.m + j] = v[k][j];
+            }
+    }
+}
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t row_lane(uint32_t x) {
+    return uint32_t(__builtin_amdgcn_update_dpp(0, int(x), CTRL, 0xf, 0xf, true));
+}
+
+// Reduction of four values over the wave at once: the 16 lanes of row q return
+// that of v[q].
+template <class Op>
+__device__ __forceinline__ uint32_t wave_reduce4(const uint32_t* v, Op op) {
+    const auto halves = [&](uint32_t a, uint32_t b) {  // lower half: a, upper half: b
+        const auto s = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+        return op(s[0], s[1]);
+    };
+    const auto s = __builtin_amdgcn_permlane16_swap(halves(v[0], v[2]), halves(v[1], v[3]), false, false);
+    uint32_t r = op(s[0], s[1]);
+    // exchange neighbours, pairs, halves of 8, halves of the row
+    r = op(r, row_lane<0xB1>(r));
+    r = op(r, row_lane<0x4E>(r));
+    r = op(r, row_lane<0x141>(r));
+    return op(r, row_lane<0x140>(r));
+}
+
 __global__ __launch_bounds__(kCodeBlock) void k_compress(const uint32_t* __restrict__ adj, int64_t n,
                                                          int64_t stride, int64_t tiles,
                                                          int16_t* __restrict__ codes,
@@ -111,52 +153,69 @@ __global__ __launch_bounds__(kCodeBlock) void k_compress(const uint32_t* __restr
     const int64_t tile = wave_tile();
     if (tile >= tiles) return;
     const int lane = int(threadIdx.x) & 63;
-    const LaneCells c = lane_cells(tile, lane, n);
-    uint32_t slot[Q - 1][4];
-    if (VEC || c.live == 4) {
-#pragma unroll
-        for (int k = 0; k < Q - 1; ++k) load4<VEC>(adj + k * stride + c.m, slot[k]);
-    } else {
-        // the list's last cells: not past the end of the last row
-#pragma unroll
-        for (int k = 0; k < Q - 1; ++k)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) slot[k][j] = adj[k * stride + (j < c.live ? c.m + j : 0)];
-    }
+    const LaneCells c(tile, lane, n);
     const uint32_t S = uint32_t(stride);
-    int32_t word = 0;  // of the tile record, lanes 0 to 19
+    // An entry that streams (it lies in row k + 1) is kept as its offset from the
+    // cell plus kZero, between 0 and 2^29 since strides are below 2^28; any
+    // other as kNone, which is below those as a signed and above them as an
+    // unsigned number.  A slot past the list lies in no row.
+    constexpr uint32_t kZero = 1u << 28, kNone = 1u << 31;
+    constexpr int kGroups = (Q - 1 + 3) / 4;
+    Slots4 e[Q - 1];
+    load_rows(adj, stride, c, ~0u, e);
+    // per direction the midpoint of the tile's smallest and largest offset (0 if
+    // nothing streams); lanes 16 q + g hold that of direction 4 g + q
+    uint32_t base[kGroups], word = 0;
+    bool wide = false;  // an offset of the tile may not fit its code
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+        uint32_t hi[4], lo[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int k = 4 * g + q;
+            hi[q] = lo[q] = kNone;
+#pragma unroll
+            for (int j = 0; j < 4 && k < Q - 1; ++j) {
+                const uint32_t col = e[k][j] - uint32_t(k + 1) * S;
+                e[k][j] = col < S ? col - (uint32_t(c.m) + j - kZero) : kNone;
+                hi[q] = uint32_t(max(int32_t(hi[q]), int32_t(e[k][j])));
+                lo[q] = min(lo[q], e[k][j]);
+            }
+        }
+        const uint32_t top = wave_reduce4(hi, [](uint32_t a, uint32_t b) {
+            return uint32_t(max(int32_t(a), int32_t(b)));
+        });
+        const uint32_t low = wave_reduce4(lo, [](uint32_t a, uint32_t b) { return min(a, b); });
+        const uint32_t span = low < kNone ? top - low : 0u;
+        base[g] = low < kNone ? low + span / 2 : kZero;
+        wide = wide || span > uint32_t(kCodeMax - kCodeMin);
+        word = (lane & 15) == g ? base[g] - kZero : word;
+    }
+    wide = __any(wide);
     uint32_t esc = 0;
+    Codes4 code[Q - 1];
 #pragma unroll
     for (int k = 0; k < Q - 1; ++k) {
-        // streaming entries lie in row k + 1: offset from the cell itself, the
-        // tile's smallest and largest, their midpoint (0 if nothing streams)
-        int32_t d[4], lo = INT32_MAX, hi = INT32_MIN;
-        bool st[4];
+        const uint32_t b = uint32_t(__builtin_amdgcn_readlane(int(base[k / 4]), 16 * (k % 4)));
+        uint32_t r[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t col = slot[k][j] - uint32_t(k + 1) * S;
-            st[j] = j < c.live && col < S;
-            d[j] = int32_t(col - uint32_t(c.m + j));
-            lo = st[j] ? min(lo, d[j]) : lo;
-            hi = st[j] ? max(hi, d[j]) : hi;
-        }
-        hi = wave_max(hi);
-        lo = ~wave_max(~lo);
-        const int32_t base = lo <= hi ? lo + int32_t((uint32_t(hi) - uint32_t(lo)) / 2) : 0;
-        word = lane == k ? base : word;
-        int16_t code[4];
+        for (int j = 0; j < 4; ++j) r[j] = int32_t(e[k][j]) < 0 ? uint32_t(kCodeBounce) : e[k][j] - b;
+        if (wide) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int32_t r = d[j] - base;  // |d|, |base| < stride < 2^28
-            const bool fits = r >= kCodeMin && r <= kCodeMax;
-            code[j] = !st[j] ? kCodeBounce : fits ? int16_t(r) : kCodeEscape;
-            esc += st[j] && !fits ? 1u : 0u;
+            for (int j = 0; j < 4; ++j) {
+                const bool escape = int32_t(e[k][j]) >= 0 && r[j] - uint32_t(kCodeMin) > uint32_t(kCodeMax - kCodeMin);
+                r[j] = escape ? uint32_t(kCodeEscape) : r[j];
+                esc += escape ? 1u : 0u;
+            }
         }
-        store4<VEC>(codes + k * stride + c.m, code, c.live);
+        code[k] = Codes4{int16_t(r[0]), int16_t(r[1]), int16_t(r[2]), int16_t(r[3])};
     }
-    for (int off = 32; off > 0; off >>= 1) esc += __shfl_xor(esc, off);
-    word = lane == Q - 1 ? int32_t(esc) : word;
-    if (lane < kRec) rec[tile * kRec + lane] = word;
+    store_rows(codes, stride, c, code);
+    if (wide)
+        for (int off = 32; off > 0; off >>= 1) esc += __shfl_xor(esc, off);
+    // the record: word 4 g + q from lane 16 q + g, then the escapes and 0
+    const int at = 4 * (lane & 15) + (lane >> 4);
+    if (at < kRec) rec[tile * kRec + at] = int32_t(at < Q - 1 ? word : at == Q - 1 ? esc : 0u);
 }
 
 // Sum of one word over all tile records in two passes: up to kSumParts
@@ -207,7 +266,6 @@ lbm_status sum_records(const int32_t* rec, int64_t tiles, int word, unsigned lon
 
 // The tile is narrow if every live cell's 18 codes fit (a tile with escapes
 // never does).  Codes of a wide tile are stored as 0.
-template <bool VEC>
 __global__ __launch_bounds__(kCodeBlock) void k_narrow(const int16_t* __restrict__ codes, int64_t n,
                                                        int64_t stride, int64_t tiles,
                                                        int32_t* __restrict__ rec,
@@ -215,34 +273,34 @@ __global__ __launch_bounds__(kCodeBlock) void k_narrow(const int16_t* __restrict
     const int64_t tile = wave_tile();
     if (tile >= tiles) return;
     const int lane = int(threadIdx.x) & 63;
-    const LaneCells c = lane_cells(tile, lane, n);
-    int16_t cd[Q - 1][4];
-    if (VEC || c.live == 4) {
-#pragma unroll
-        for (int k = 0; k < Q - 1; ++k) load4<VEC>(codes + k * stride + c.m, cd[k]);
-    } else {
-#pragma unroll
-        for (int k = 0; k < Q - 1; ++k)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) cd[k][j] = codes[k * stride + (j < c.live ? c.m + j : 0)];
-    }
-    bool fits = true;
-#pragma unroll
-    for (int k = 0; k < Q - 1; ++k)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int32_t v = cd[k][j];
-            fits = fits && (j >= c.live || v == kCodeBounce || (v >= -kCode8Max && v <= kCode8Max));
-        }
-    const bool narrow = __all(fits);
+    const LaneCells c(tile, lane, n);
+    Codes4 cd[Q - 1];
+    load_rows(codes, stride, c, kCodeBounce, cd);
+    // the largest of every code and its negative; the code of a bounce-back,
+    // -2^15, is its own negative in 16 bits
+    Pair size = {0, 0};
+    const auto grow = [&](Pair v) {
+        typedef uint16_t Bits __attribute__((ext_vector_type(2)));
+        const Pair neg = __builtin_bit_cast(Pair, Bits{0, 0} - __builtin_bit_cast(Bits, v));
+        size = __builtin_elementwise_max(size, __builtin_elementwise_max(v, neg));
+    };
 #pragma unroll
     for (int k = 0; k < Q - 1; ++k) {
-        int8_t v[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            v[j] = !narrow ? int8_t(0) : cd[k][j] == kCodeBounce ? kCode8Bounce : int8_t(cd[k][j]);
-        store4<VEC>(codes8 + k * stride + c.m, v, c.live);
+        grow(cd[k].xy);
+        grow(cd[k].zw);
     }
+    const bool narrow = __all(max(size.x, size.y) <= kCode8Max);
+    // the low byte of a code, of -128 for a bounce-back
+    const auto bytes_of = [](Pair v) {
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(v, Pair{kCode8Bounce, kCode8Bounce}));
+    };
+    Bytes4 bytes[Q - 1];
+#pragma unroll
+    for (int k = 0; k < Q - 1; ++k) {
+        const uint32_t four = __builtin_amdgcn_perm(bytes_of(cd[k].zw), bytes_of(cd[k].xy), 0x06040200u);
+        bytes[k] = __builtin_bit_cast(Bytes4, narrow ? four : 0u);
+    }
+    store_rows(codes8, stride, c, bytes);
     if (lane == 0) rec[tile * kRec + Q] = narrow ? 1 : 0;
 }
 
@@ -361,10 +419,7 @@ extern "C" lbm_status lbm_compress_adjacency(int64_t n, int64_t stride, const ui
     auto* ws = static_cast<unsigned long long*>(workspace);
     const int64_t tiles = (n + kCTile - 1) / kCTile;
     const unsigned grid = unsigned((tiles + kCodeBlock / 64 - 1) / (kCodeBlock / 64));
-    if (rows_of_4(stride, adj, sizeof(*adj)) && rows_of_4(stride, codes, sizeof(*codes)))
-        k_compress<true><<<grid, kCodeBlock, 0, s>>>(adj, n, stride, tiles, codes, tile_records);
-    else
-        k_compress<false><<<grid, kCodeBlock, 0, s>>>(adj, n, stride, tiles, codes, tile_records);
+    k_compress<<<grid, kCodeBlock, code_lds(n), s>>>(adj, n, stride, tiles, codes, tile_records);
     if (hipGetLastError() != hipSuccess) return LBM_EHIP;
     if (lbm_status st = sum_records(tile_records, tiles, Q - 1, ws, s); st != LBM_OK) return st;
     unsigned long long e = 0;
@@ -403,10 +458,7 @@ extern "C" lbm_status lbm_narrow_codes(int64_t n, int64_t stride, const int16_t*
     auto* ws = static_cast<unsigned long long*>(workspace);
     const int64_t tiles = (n + kCTile - 1) / kCTile;
     const unsigned grid = unsigned((tiles + kCodeBlock / 64 - 1) / (kCodeBlock / 64));
-    if (rows_of_4(stride, codes, sizeof(*codes)) && rows_of_4(stride, codes8, sizeof(*codes8)))
-        k_narrow<true><<<grid, kCodeBlock, 0, s>>>(codes, n, stride, tiles, tile_records, codes8);
-    else
-        k_narrow<false><<<grid, kCodeBlock, 0, s>>>(codes, n, stride, tiles, tile_records, codes8);
+    k_narrow<<<grid, kCodeBlock, code_lds(n), s>>>(codes, n, stride, tiles, tile_records, codes8);
     if (hipGetLastError() != hipSuccess) return LBM_EHIP;
     if (lbm_status st = sum_records(tile_records, tiles, Q, ws, s); st != LBM_OK) return st;
     unsigned long long t = 0;
