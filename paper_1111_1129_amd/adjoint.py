@@ -88,7 +88,9 @@ def forward_states(lat: Lattice, prm, ns: torch.Tensor, T: int, k: int,
             # one checkpoint: copied, since the state's two arrays are one
             # allocation, which a checkpoint in it would hold whole
             ckpts.append(cur.clone())
-            cur, spare = steps.advance(cur, spare, cur, n)
+            steps.sweeps(cur, spare, n)
+            if n % 2:
+                cur, spare = spare, cur
         else:
             # the array that holds the state is the checkpoint (nothing writes
             # it again); the segment goes on in two others and ends in the
