@@ -1,5 +1,5 @@
-"""Every sweep form over lists larger than the last-level cache, where the
-streaming kernels run: with and without launch hints, with a solid fraction,
+"""Every sweep form over lists larger than the last-level cache, or that it holds
+most of, where the streaming kernels run: with and without launch hints, with a solid fraction,
 over a list with narrow, 16-bit and escape tiles, with parameter sets, and the
 adjoint in both of its builds.
 
@@ -145,6 +145,42 @@ def test_sweeps_of_a_large_list(large, storage, pbb):
             else:
                 L.step_c8(st, comp, STEPS, persistent=form == "persistent")
             assert torch.equal(st.f[:, :n], a[:, :n]), (form, nt, chunk)
+
+
+# States that the cache holds most of: one run per XCD, plain stores, alternating
+# directions without hints; (storage, third edge of the list's parts, forms)
+NEAR = [("f64s", 60, ("full", "c16")), ("f64s", 120, ("inplace",)),
+        ("f32s", 120, ("full", "c16")), ("f16s12", 120, ("full",))]
+
+
+@pytest.mark.parametrize("pbb", [False, True])
+@pytest.mark.parametrize("storage,scale,forms", NEAR)
+def test_sweeps_of_a_list_near_the_cache(storage, scale, forms, pbb):
+    lat, comp, ranges = mixed_list(scale)
+    n, pieces = lat.n_fluid, Pieces(lat, ranges)
+    ns = solid(lat) if pbb else None
+    prm = L.params(0.8, 3 / 16, (1e-5, 2e-6, 0), storage)
+    dtype = N.STORAGE_DTYPE[prm.storage]
+    f0 = noise((19, n), 5, dtype)
+    a, b = (torch.zeros((19, lat.stride), dtype=dtype, device="cuda") for _ in range(2))
+    a[:, :n] = f0
+    for _ in range(STEPS):
+        pieces.step(lambda _: prm, ns, a, b)
+        a, b = b, a
+    for form in forms:
+        in_place = form == "inplace"
+        launch = N.lbm_sweep_launch(prm, n, STEPS, 2 if form == "c16" else 4, in_place)[1]
+        print_case("near the cache", storage, scale, pbb, form, launch)
+        assert launch == (0, 1, 1)
+        st = (L.init_inplace if in_place else L.init)(lat, prm, ns=ns)
+        st.f[:, :n] = f0
+        if in_place:
+            L.step_inplace(st, STEPS)
+        elif form == "full":
+            L.step(st, STEPS)
+        else:
+            L.step_c16(st, comp, STEPS)
+        assert torch.equal(st.f[:, :n], a[:, :n]), form
 
 
 @pytest.mark.parametrize("persistent", [False, True])
