@@ -324,7 +324,7 @@ lbm_status launch_table_steps(const BatchLaunch& L, const SweepLaunch& l, hipStr
     using T = typename Storage<ST>::T;
     T* a = static_cast<T*>(L.fa);
     T* b = static_cast<T*>(L.fb);
-    const BoundKernel kernel(k_trt_table<ST, PBB, POL, SRC>, l.grid, l.block, s);
+    const BoundKernel kernel(k_trt_table<ST, PBB, POL, SRC>, l.grid, l.block, s, L.n_steps);
     for (int k = 0; k < L.n_steps; ++k) {
         const T* src = (k & 1) ? b : a;
         T* dst = (k & 1) ? a : b;

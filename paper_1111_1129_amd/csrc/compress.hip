@@ -365,12 +365,12 @@ lbm_status launch_coded(const lbm_params& p, int64_t n, int64_t stride, const in
             return LBM_OK;
         };
         if (codes8) {
-            const BoundKernel kernel(k_trt_c8<ST, PBB, pol>, l.grid, l.block, s);
+            const BoundKernel kernel(k_trt_c8<ST, PBB, pol>, l.grid, l.block, s, n_steps);
             return steps([&](const T* src, T* dst, XcdMap map) {
                 return kernel(src, dst, codes8, codes, toff, adj, ns, n, stride, c, map);
             });
         }
-        const BoundKernel kernel(k_trt_c16<ST, PBB, pol>, l.grid, l.block, s);
+        const BoundKernel kernel(k_trt_c16<ST, PBB, pol>, l.grid, l.block, s, n_steps);
         return steps([&](const T* src, T* dst, XcdMap map) {
             return kernel(src, dst, codes, toff, adj, ns, n, stride, c, map);
         });

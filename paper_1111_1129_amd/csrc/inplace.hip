@@ -157,11 +157,12 @@ lbm_status launch_inplace(const lbm_params& p, int64_t n, int64_t stride, const 
     const TrtConst c = make_trt_const(p);
     const SweepLaunch l = inplace_launch<ST>(p.flags, n, codes8 ? 1 : codes ? 2 : 4, n_steps);
     return with_policy(l.policy, [&](auto pol) -> lbm_status {
-        const BoundKernel local(k_local<ST, PBB, pol>, l.grid, l.block, s);
+        const int home_steps = (n_steps + (phase & 1)) / 2;
+        const BoundKernel local(k_local<ST, PBB, pol>, l.grid, l.block, s, home_steps);
         const BoundKernel scatter(codes8  ? k_gather_scatter<ST, PBB, pol, kFrom8>
                                   : codes ? k_gather_scatter<ST, PBB, pol, kFrom16>
                                           : k_gather_scatter<ST, PBB, pol, kFromAdj>,
-                                  l.grid, l.block, s);
+                                  l.grid, l.block, s, n_steps - home_steps);
         for (int k = 0; k < n_steps; ++k) {
             const bool at_home = (phase + k) & 1;
             const XcdMap map = l.towards(at_home);

@@ -96,7 +96,7 @@ lbm_status launch_steps(const lbm_params& p, int64_t n, int64_t stride, const ui
     const TrtConst c = make_trt_const(p);
     const SweepLaunch l = two_array_launch<ST>(p.flags, n, sizeof(uint32_t), n_steps);
     return with_policy(l.policy, [&](auto pol) -> lbm_status {
-        const BoundKernel kernel(k_trt<ST, PBB, pol>, l.grid, l.block, s);
+        const BoundKernel kernel(k_trt<ST, PBB, pol>, l.grid, l.block, s, n_steps);
         for (int k = 0; k < n_steps; ++k) {
             const T* src = (k & 1) ? b : a;
             T* dst = (k & 1) ? a : b;
