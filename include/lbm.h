@@ -99,9 +99,11 @@ typedef enum {
 enum {
     /* Launch hints.  Results do not depend on them.  Without any (neither this
      * flag nor the XCD chunk bits) the library chooses by storage, form and size.
-     * With one it follows them, except that a call of at least 8 sweeps keeps a
-     * state of up to 240 MiB (with the codes or the list that are read) in the
-     * last-level cache and needs none; lbm_sweep_launch tells what a call uses. */
+     * With one it follows them, except in a call of two sweeps or more over a state
+     * that the last-level cache holds, or holds most of, from sweep to sweep: up
+     * to 240 MiB with the codes or the list that are read, and up to 384 MiB over
+     * 16-bit codes (two arrays) and 512 MiB over the list.  lbm_sweep_launch tells
+     * what a call uses. */
     LBM_FLAG_NONTEMPORAL = 1, /* write the new PDFs with nontemporal stores (Sec. 7);
                                  large FP64 states and sweeps over 8-bit codes have
                                  them without it too */
@@ -325,7 +327,8 @@ lbm_status lbm_step_batch(const lbm_params* p, int32_t n_params, const lbm_segme
  *  lam_next double [19][stride] or NULL; lam_t double [19][stride] (output).
  *  grad_ns  double [stride], accumulated (+=); caller zeroes it.
  *  p->flags the sweep's launch options apply (nontemporal stores of lam_t,
- *           workgroup-to-XCD mapping); results do not depend on them.
+ *           workgroup-to-XCD mapping) to more than 400,000 cells or so, whose
+ *           arrays the last-level cache cannot hold; results do not depend on them.
  * Errors: LBM_EINVAL (NULL p/adj/f_t/lam_t, n <= 0, stride < n, storage not
  * FP64), LBM_EOVERFLOW, LBM_EHIP.
  */

@@ -24,6 +24,15 @@ from .checkpointing import Revolve
 from .lattice import Compressed, Lattice, compress, init, narrow, objective
 
 
+def _run_params(prm, n: int):
+    """prm for the single sweeps of a longer run: without launch hints where a
+    call of several sweeps over n cells would not follow them."""
+    quiet = N.lbm_params.from_buffer_copy(prm)
+    quiet.flags &= ~(N.FLAG_NONTEMPORAL | 0xff << N.FLAG_XCD_CHUNK_SHIFT)
+    same = N.lbm_sweep_launch(prm, n, 2, 1) == N.lbm_sweep_launch(quiet, n, 2, 1)
+    return quiet if same else prm
+
+
 class _Steps:
     """Sweeps and adjoint steps over the first n cells of a list and its codes,
     on the stream that is current when this is made.  What does not change from call to call
@@ -31,11 +40,13 @@ class _Steps:
 
     def __init__(self, lat: Lattice, n: int, prm, comp: Compressed, ns: torch.Tensor | None):
         lib = N.load()
-        self.keep = (lat, prm, comp, ns)
-        head = (C.byref(prm), n, lat.stride, comp.codes8.data_ptr(),
-                comp.codes.data_ptr(), comp.tile_records.data_ptr(), lat.adj.data_ptr())
+        run_prm = _run_params(prm, n)
+        self.keep = (lat, prm, run_prm, comp, ns)
+        lists = (n, lat.stride, comp.codes8.data_ptr(), comp.codes.data_ptr(),
+                 comp.tile_records.data_ptr(), lat.adj.data_ptr())
         ns_ptr, stream = N._ptr(ns), N._stream()
         step, adjoint = lib.lbm_step_c8, lib.lbm_step_adjoint_c8
+        head, adjoint_head = (C.byref(run_prm), *lists), (C.byref(prm), *lists)
 
         def sweeps(src: torch.Tensor, dst: torch.Tensor, k: int = 1):
             """k sweeps from src, alternating between dst and src (dst first)."""
@@ -44,8 +55,8 @@ class _Steps:
                 N._check("lbm_step_c8", rc)
 
         def adjoint_step(f_t, lam_next, lam_t, grad):
-            rc = adjoint(*head, f_t.data_ptr(), ns_ptr, lam_next.data_ptr(), lam_t.data_ptr(),
-                         grad.data_ptr(), stream)
+            rc = adjoint(*adjoint_head, f_t.data_ptr(), ns_ptr, lam_next.data_ptr(),
+                         lam_t.data_ptr(), grad.data_ptr(), stream)
             if rc:
                 N._check("lbm_step_adjoint_c8", rc)
 

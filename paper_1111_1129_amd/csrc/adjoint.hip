@@ -28,10 +28,12 @@ constexpr size_t kAdjCellBytes = 4 * Q * sizeof(double);
 
 // Beyond 384 MiB steps with plain stores alternate their direction (8-bit codes,
 // 0.96 / 1.5 / 2.0 / 3.3 / 7.8 M cells 87.6 / 157.8 / 194.9 / 332.9 / 771 -> 84.4 /
-// 147.9 / 182.1 / 323.7 / 766 us).
+// 147.9 / 182.1 / 323.7 / 766 us).  A step is one of a reverse sweep over the same
+// arrays: where those stay in the cache it takes no hints, like a call of several
+// sweeps.
 inline SweepLaunch adjoint_launch(int32_t flags, int64_t n) {
     constexpr SweepRule rule = {size_t(384) << 20, false, false, false};
-    return sweep_launch(flags, n, kAdjCellBytes, rule, 1);
+    return sweep_launch(flags, n, kAdjCellBytes, rule, kResidentSweeps);
 }
 
 // Waves per SIMD that the kernels are built for.  A cell holds 38 gathered and

@@ -363,13 +363,13 @@ __host__ __device__ inline int64_t virtual_blocks(int64_t blocks, XcdMap map) {
 //    list at 165 MB 25.9 / 32.7, at 41 MB 8.0 / 10.6).
 //  * that holds for a state that is swept again before others have passed
 //    through the cache.  Only the caller knows whether it is, so hints are
-//    followed in calls of fewer than 8 sweeps; from there on the call itself
-//    brings the state in (six states of 200 MiB in turn, us a sweep, hints
-//    followed / kCached, by sweeps of a call: shifted FP32 over 16-bit codes
-//    1: 38.2 / 43.2, 2: 38.0 / 42.2, 8: 35.0 / 30.9 at 180 MiB; in place over
-//    8-bit codes, runs of 16 tiles, 1: 66.6 / 73.4, 2: 55.9 / 60.9, 4: 50.7 /
-//    53.2 and 8: 50.7 / 50.8 at 180 MiB; 15 forms of 30 to 235 MiB at 8 sweeps,
-//    one state or six in turn: -31 to 0 %).
+//    followed in calls of one sweep; from two on the call itself brings the state
+//    in.  Time with hints followed over this form (FP64, shifted FP32, scaled
+//    FP16, five forms, 30 to 240 MiB, hints of nontemporal stores and 1, 8, 64
+//    tiles or none; smallest / median / largest): one state, calls of 1 or 2
+//    sweeps, 0.94 / 1.24 / 1.51 and 1.02 / 1.26 / 1.50; as many states in turn as
+//    take 1.2 GB, calls of 1, 2 or 4 sweeps, 0.89 / 0.99 / 1.33, 0.91 / 1.07 /
+//    1.33 and 0.98 / 1.16 / 1.44.
 //  * from there to SweepRule::whole_runs the cache still holds most of it.
 //    Without hints one run per XCD and plain stores; the two-array sweep
 //    alternates its direction, so that a sweep begins with what the one before
@@ -385,10 +385,12 @@ __host__ __device__ inline int64_t virtual_blocks(int64_t blocks, XcdMap map) {
 //    80.1 and 49.2 / 59.7 / 72.5, shifted FP32 at 257 / 278 / 341 / 397 MB 41.9 /
 //    55.5 / 70.0 / 84.4 and 48.4 / 51.6 / 62.8 / 74.4, scaled FP16 at 255 / 299 /
 //    376 MB 45.8 / 66.5 / 84.8 and 53.2 / 63.3 / 77.4).
-//    Hints are followed, whatever the call: which form is faster depends on
-//    what else passes through the cache (scaled FP16 full list at 300 MiB, one
-//    state / six in turn, hints followed 54.9 / 54.8, this form 58.5 / 73.3;
-//    FP64 full list at 450 MiB 86.9 / 86.7 and 79.2 / 93.2).
+//    The forms that alternate take no hints either in calls of two sweeps and
+//    more (the same storages over the list, over 16-bit codes and in place over
+//    the list, 2 to 4 sizes each: one state, calls of 2 sweeps, 0.91 / 1.11 /
+//    1.23; three states in turn, calls of 2 or of 8 and 20 sweeps, 0.81 / 0.96 /
+//    1.08 and 0.89 / 1.08 / 1.24; what is below 0.91 are FP64 over 16-bit codes
+//    at 343 MiB and in place at 395 MiB).
 //  * beyond it, runs of as many tiles as the LBM_FLAG_XCD_CHUNK bits say, or,
 //    without them, of 8 tiles: the XCDs sweep nearby parts of the list together
 //    (DRAM pages) and are evenly loaded (FP64 full list, 7.5 M cells: 525 us
@@ -405,11 +407,12 @@ __host__ __device__ inline int64_t virtual_blocks(int64_t blocks, XcdMap map) {
 //    (shifted FP32 612 MB 113.4 -> 108.7 us, FP64 402 MB 77.4 -> 74.0);
 //    nontemporal over the other forms -1 to +2 %, so those keep one direction.
 constexpr size_t kCachedBytes = size_t(240) << 20;
-constexpr int kResidentSweeps = 8;
+constexpr int kResidentSweeps = 2;
 
 struct SweepRule {
     size_t whole_runs;     // bytes up to which an XCD takes one run
-    bool alternate_whole;  // up to there directions alternate without hints
+    bool alternate_whole;  // up to there directions alternate, in calls of several
+                           // sweeps whatever the hints
     bool nt;               // nontemporal stores beyond it also without the flag
     bool alternate_nt;     // directions alternate with nontemporal stores too
 };
@@ -439,9 +442,12 @@ inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, con
     const size_t bytes = size_t(n) * cell_bytes;
     const int64_t blocks = std::max<int64_t>(1, (n + block - 1) / block);
     const bool hinted = flags & (LBM_FLAG_NONTEMPORAL | LBM_FLAG_XCD_CHUNK_MASK);
-    const bool cached = bytes <= kCachedBytes && (!hinted || n_steps >= kResidentSweeps);
+    const bool resident = !hinted || n_steps >= kResidentSweeps;
+    const bool cached = bytes <= kCachedBytes && resident;
     const bool large = bytes > rule.whole_runs;
-    const int64_t given = cached ? 0 : (flags & LBM_FLAG_XCD_CHUNK_MASK) >> LBM_FLAG_XCD_CHUNK_SHIFT;
+    const bool whole = !cached && !large && rule.alternate_whole && resident;
+    if (cached || whole) flags = 0;
+    const int64_t given = (flags & LBM_FLAG_XCD_CHUNK_MASK) >> LBM_FLAG_XCD_CHUNK_SHIFT;
     SweepLaunch l;
     l.blocks = uint32_t(blocks);
     l.run = int32_t(given ? given : large ? 8 : 0);
@@ -455,7 +461,7 @@ inline SweepLaunch sweep_launch(int32_t flags, int64_t n, size_t cell_bytes, con
     }
     const bool nt = (flags & LBM_FLAG_NONTEMPORAL) || (large && rule.nt);
     l.policy = cached ? kCached : nt ? kStreamNT : kStream;
-    l.alternate = !cached && (large ? !nt || rule.alternate_nt : rule.alternate_whole && !hinted);
+    l.alternate = large ? !nt || rule.alternate_nt : whole;
     l.grid = dim3(unsigned(virtual_blocks(blocks, l.map)));
     l.block = dim3(unsigned(block));
     return l;

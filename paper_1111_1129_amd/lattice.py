@@ -125,8 +125,9 @@ def params(tau_plus=0.8, magic=3.0 / 16.0, force=(0.0, 0.0, 0.0), storage="f64",
            nontemporal=False, xcd_chunk=0) -> N.lbm_params:
     """TRT parameters.  xcd_chunk: consecutive list tiles per XCD (a power of
     two; 1 = hardware round robin, 0 = chosen by the library from the size).
-    Both are launch hints; without either the library chooses.  A call of at
-    least 8 sweeps over a state that fits the last-level cache needs none."""
+    Both are launch hints; without either the library chooses, as it does in a
+    call of two sweeps or more over a state that the last-level cache holds
+    or holds most of (lbm_sweep_launch)."""
     assert xcd_chunk >= 0 and xcd_chunk & (xcd_chunk - 1) == 0 and xcd_chunk < 256
     flags = (N.FLAG_NONTEMPORAL if nontemporal else 0) | (xcd_chunk << N.FLAG_XCD_CHUNK_SHIFT)
     return N.make_params(tau_plus, magic, force, storage, flags)

@@ -1,6 +1,7 @@
 """The launch that the hints and the size of a state come to (CPU): hints are
-followed at every size, except that a call of at least 8 sweeps keeps a state of
-up to 240 MiB in the last-level cache; without hints the library chooses."""
+followed at every size, except in a call of two sweeps or more over a state that
+the last-level cache holds (up to 240 MiB) or, for the forms that then alternate
+their direction, holds most of; without hints the library chooses."""
 import pytest
 
 from paper_1111_1129_amd import _native as N
@@ -23,6 +24,7 @@ def launch(storage, code_bytes, in_place, n, steps, nt=False, chunk=0):
     return out
 
 
+WHOLE = {(4, False): 512, (4, True): 512, (2, False): 384, (1, False): 256}
 FORMS = [(c, p) for c in (4, 2, 1) for p in (False, True)]
 
 
@@ -32,21 +34,24 @@ def test_hints_are_followed(storage, code_bytes, in_place):
     for mib in (1, 60, 200, 240, 241, 300, 375, 450, 511, 600, 4000):
         n = cells(storage, code_bytes, in_place, mib)
         for steps in (1, 2, 7, 8, 100):
-            kept = mib <= 240 and steps >= 8
+            kept = mib <= 240 and steps >= 2
+            whole = 240 < mib <= WHOLE.get((code_bytes, in_place), 0) and steps >= 2
             for chunk in (1, 2, 16, 128):
                 for nt in (False, True):
                     run, stores, alternate = launch(storage, code_bytes, in_place, n, steps, nt, chunk)
-                    assert run == (EIGHTHS if kept else chunk)
+                    assert run == (EIGHTHS if kept or whole else chunk)
                     if kept:
                         assert stores == CACHED and not alternate
+                    elif whole:
+                        assert stores == PLAIN and alternate
                     elif nt:
                         assert stores == NONTEMPORAL
                     else:
                         assert stores in (PLAIN, NONTEMPORAL)
-                    if mib <= 250:
+                    if mib <= 250 and not whole:
                         assert not alternate
             assert launch(storage, code_bytes, in_place, n, steps, True)[1] == (
-                CACHED if kept else NONTEMPORAL)
+                CACHED if kept else PLAIN if whole else NONTEMPORAL)
 
 
 @pytest.mark.parametrize("storage", sorted(WIDTH))
